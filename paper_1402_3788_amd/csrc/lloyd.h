@@ -17,14 +17,17 @@ constexpr int kCUs = 256;            // compute units the launch geometry is siz
 
 // Iteration control block, kept at the start of the caller's workspace.
 //   changed[t & 1] : set by the centres launch of iteration t (each of its
-//                    workgroups ORs in 1 when one of its centre coordinates
+//                    workgroups stores 1 when one of its centre coordinates
 //                    differs bitwise from t-1's; the centres launch of t-1
-//                    cleared it).
+//                    cleared it). Not kept by runs of a fixed number of
+//                    iterations.
 //   converged_at   : first t >= 2 whose centres were congruent with t-1's
 //                    (0 = not yet); written by the launches of iteration t+1.
-//   fallbacks      : objects whose label was re-decided in fp64 (diagnostic).
-//   reruns         : wave tiles whose split-precision scores left a call too
-//                    close, recomputed with fp32 products (diagnostic).
+//   fallbacks      : objects whose label the scores left open, decided again
+//                    (diagnostic).
+//   reruns         : columns of up to 16 such objects that the tile kernel
+//                    gathered and scored again, and batches of up to 64 that
+//                    it decided without (diagnostic).
 //   ring_stalls    : waves of the tile kernel's ring form whose wait for their
 //                    turn gave up (never expected; the sums are then unordered
 //                    and kmeans_run fails with KMEANS_EHIP).
@@ -69,8 +72,10 @@ enum Mode : int {
 // Distance paths: one object per lane with the direct form on the vector ALU
 // (lloyd_lane.hip), one object per lane with the scores on the bf16 matrix
 // cores (lloyd_lane_mfma.hip, K <= 16), or 64-object tiles on the matrix cores
-// with a cross-lane argmin (lloyd_tile.hip, any K).
-enum Path : int { kPathValu = 0, kPathTile = 1, kPathLaneMfma = 2 };
+// with a cross-lane argmin (lloyd_tile.hip, any K). kPathSplit: the tile
+// kernel assigns only, and the sums come from its labels in a launch of their
+// own (lloyd_accum.hip).
+enum Path : int { kPathValu = 0, kPathTile = 1, kPathLaneMfma = 2, kPathSplit = 3 };
 
 // Static LDS of a kernel (bytes), from the runtime's attributes; SIZE_MAX when
 // they cannot be read. Launches check static + dynamic LDS against kMaxLds, so
@@ -94,6 +99,10 @@ struct AccumPlan {
 AccumPlan plan_lane(int64_t n, int M, int K, Mode mode);
 AccumPlan plan_lane_mfma(int64_t n, int M, int K, Mode mode);
 AccumPlan plan_tile(int64_t n, int M, int K, Mode mode);
+// The accumulating launch of kPathSplit (accum: its feature slices).
+AccumPlan plan_accum(int64_t n, int M, int K);
+// Waves per workgroup of the tile kernel (0: its state does not fit in LDS).
+int tile_waves(int M, int K, Mode mode);
 // Whether the tile kernel's per-workgroup state (centre operands and fp64
 // slab) fits in one workgroup's LDS for this shape.
 bool tile_fits(int M, int K);
@@ -126,6 +135,9 @@ struct StepArgs {
 hipError_t launch_lane(const StepArgs &a, Mode mode, const AccumPlan &plan, hipStream_t s);
 hipError_t launch_lane_mfma(const StepArgs &a, Mode mode, const AccumPlan &plan, hipStream_t s);
 hipError_t launch_tile(const StepArgs &a, Mode mode, const AccumPlan &plan, hipStream_t s);
+
+// The sums of Eq. (1) from a.labels_in (kPathSplit).
+hipError_t launch_accum(const StepArgs &a, const AccumPlan &plan, hipStream_t s);
 
 hipError_t launch_ctl_reset(Ctl *ctl, hipStream_t s);
 

@@ -424,10 +424,11 @@ __device__ inline void accumulate_commit(int lab, const AccFetch<M, P_> &f, int3
 // Workgroup partial of the wave-accumulation form: for every (cluster, feature)
 // the sum over waves w and slabs h (w, then h, ascending) written to
 // part_sums[K][M], and the count of cluster k to counts_col[k * cstride] (the
-// workgroup's column of the [K][G] count table). Call after a barrier.
+// workgroup's column of the [K][G] count table). `rows_per_slab` is the slabs'
+// row count (K, or more with spare rows). Call after a barrier.
 // kShared: one slab per wave (see accumulate_tile).
 template <int M, int P_, bool kShared = false>
-__device__ inline void write_wave_partials(const double *slabs, int W, int K,
+__device__ inline void write_wave_partials(const double *slabs, int W, int K, int rows_per_slab,
                                            double *__restrict__ part_sums,
                                            int32_t *__restrict__ counts_col, int cstride)
 {
@@ -438,7 +439,7 @@ __device__ inline void write_wave_partials(const double *slabs, int W, int K,
     for (int e = tid; e < K * MW; e += nthr) {
         const int k = e / MW, j = e - (e / MW) * MW;
         double s = 0.0;
-        for (size_t r = 0; r < rows; ++r) s = s + slabs[(r * K + k) * MW + j];
+        for (size_t r = 0; r < rows; ++r) s = s + slabs[(r * rows_per_slab + k) * MW + j];
         if (j < M) part_sums[(int64_t)k * M + j] = s;
         else counts_col[(int64_t)k * cstride] = (int32_t)s;
     }

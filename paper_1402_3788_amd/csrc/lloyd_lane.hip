@@ -255,7 +255,7 @@ lloyd_lane_kernel(const float *__restrict__ X, int64_t n, const float *__restric
 
     if (MODE != kAssign) {
         __syncthreads();
-        write_wave_partials<M, PA>(slabs_all, W, K, part_sums + (int64_t)blockIdx.x * K * M,
+        write_wave_partials<M, PA>(slabs_all, W, K, K, part_sums + (int64_t)blockIdx.x * K * M,
                                    part_counts + blockIdx.x, gridDim.x);
     }
 }
@@ -320,11 +320,8 @@ constexpr int kPartN = kMaxM / LLOYD_PARTS;
 template <int M>
 constexpr LaunchFn entry()
 {
-#ifdef LLOYD_ONLY_M
-    if constexpr (M != LLOYD_ONLY_M) return nullptr;
-    else
-#endif
-    return &launch_m<M>;
+    if constexpr (!lloyd_built(M)) return nullptr;
+    else return &launch_m<M>;
 }
 
 template <int... Is>
@@ -336,11 +333,8 @@ constexpr auto make_table(std::integer_sequence<int, Is...>)
 template <int M>
 constexpr LaunchL1Fn entry_l1()
 {
-#ifdef LLOYD_ONLY_M
-    if constexpr (M != LLOYD_ONLY_M) return nullptr;
-    else
-#endif
-    return &launch_l1_m<M>;
+    if constexpr (!lloyd_built(M)) return nullptr;
+    else return &launch_l1_m<M>;
 }
 
 template <int... Is>

@@ -800,11 +800,7 @@ constexpr int kPartN = kMaxM / LLOYD_PARTS;
 template <int M>
 constexpr LaunchFn entry()
 {
-#ifdef LLOYD_ONLY_M
-    if constexpr (M != LLOYD_ONLY_M) return nullptr;
-    else
-#endif
-    if constexpr (M <= kMaxMLane) return &launch_m<M>;
+    if constexpr (M <= kMaxMLane && lloyd_built(M)) return &launch_m<M>;
     else return nullptr;
 }
 

@@ -9,22 +9,33 @@
 // once per workgroup in LDS, in the lane order the instruction wants), B = X^T
 // (read from the LDS tile) and the accumulator seeded with |c|^2, in up to
 // three stages:
-//   pass 1 (every tile): split precision on the bf16 matrix cores, three
-//     v_mfma_f32_16x16x32_bf16 per block on operands split into bf16 hi and
-//     lo parts rounded to nearest; each score is within E (3|c|^2 + |x|^2) of
-//     the exact one (E = 3.02 * 2^-16 + 1.01 (96 ceil(M/32) + 2 + M/6) 2^-23,
-//     assuming only that the matrix core rounds each addition faithfully); the
-//     scores are scanned as packed (score, index) keys, and a label is
-//     accepted when the two best keys differ by more than twice that bound
-//     plus the keys' truncation (with |c|^2 bounded by the largest centre
-//     norm and margins);
-//   pass 2 (tiles with a call too close for pass 1): fp32 products, a
-//     v_mfma_f32_16x16x4f32 chain over the features, whose error is bounded by
-//     1.01 (4 ceil(M/4) + 3 + M/6) 2^-23 (3|c|^2 + |x|^2) under the same
-//     assumption (each product and each addition rounded faithfully); a label
-//     is accepted at 2.02 times that;
-//   the objects still too close are re-decided with fp64 distances in the
-//   fixed operation order, over all centres, lowest index on ties.
+//   pass 1 (every tile): split precision on the bf16 matrix cores, operands
+//     split into bf16 hi and lo parts rounded to nearest. 32 features take
+//     three v_mfma_f32_16x16x32_bf16 per block (lo.hi, hi.lo, hi.hi); a last
+//     chunk of at most 16 features puts hi and lo of A side by side in one
+//     operand and takes two (against B's lo, then hi), one of at most 8
+//     features puts both parts of both sides in one product. Each score is
+//     within E (3|c|^2 + |x|^2) of the exact one (E below, assuming only that
+//     the matrix core rounds each addition faithfully); the scores are scanned
+//     as packed (score, index) keys, and a label is accepted when the two best
+//     keys differ by more than twice that bound plus the keys' truncation
+//     (with |c|^2 bounded by the largest centre norm and margins);
+//   the other objects (close calls) stay out of the sums; the wave notes them,
+//   each with its limit (best key + threshold: no centre whose score is above
+//   it can be the nearest), in a list in LDS, and the workgroup decides them
+//   after its last tile, in columns of 16: their scores are formed again, the
+//   centres within the limit become candidates, and the fp64 distances to
+//   those (the fixed operation order, lowest index on ties) decide. Objects
+//   with more than four candidates in one lane, and all objects of a wave whose
+//   list overflowed (they are then found again by the negative mark left in
+//   their labels), take the direct fp32 form over all centres, and fp64 over
+//   all centres where that leaves a gap below 4 gamma_{M+2}.
+//
+// Why the close calls wait: on data whose clusters overlap a tenth of the
+// objects is close, so almost every 64-object tile holds one. Recomputing such
+// a tile with fp32 products and fp64 distances to every centre took 470 of
+// the 620 us of a launch (n = 1e6, M = 37, K = 100); gathered, they cost a
+// column each, and the streaming loop keeps no code or registers for them.
 //
 // Layout of the 16x16 products (64 lanes): D[i][j] is in lane j + 16(i/4),
 // register i%4; A[i][k] in lane i + 16k (16x16x4) or lane i + 16(k/8), element
@@ -34,7 +45,7 @@
 // results with row swaps (v_permlane16_swap, v_permlane32_swap).
 //
 // Each wavefront streams 64-object tiles (in wave-major rounds of the grid):
-// the next two tiles' loads are in flight in registers while the current tile
+// the next tile's loads are in flight in registers while the current tile
 // is staged in the wave's LDS slot; the round with the ragged last tile (n not
 // a multiple of 64) is handled after the loop.
 //
@@ -45,7 +56,7 @@
 //              one slab per object of a step, or (when that leaves fewer
 //              waves) one slab that the objects of a step share, the LDS
 //              applying the lanes of one add in a fixed order; at the end the
-//              workgroup adds the slabs in a fixed order. Used while W >= 4
+//              workgroup adds the slabs in a fixed order. Used while W >= 6
 //              waves' private slabs fit in LDS (small K*M).
 //   ring    -- one fp64 slab per workgroup that the waves take turns to add
 //              their tiles into, in the fixed cyclic order wave 0, 1, ..., W-1
@@ -70,6 +81,8 @@ namespace lloyd {
 namespace {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
+// Four floats at any 4-byte-aligned address: rows of X start on any float.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kCols = 4;      // 16-object columns per wave tile (64 objects)
 // Index bits of a packed key: enough for the (padded) centres, at most 8;
@@ -82,17 +95,41 @@ constexpr int kAccWave = 1;    // per-wave slabs, WaveAcc<M>::Pmax objects per s
 constexpr int kAccRing = 2;    // one slab per workgroup, waves add in turn
 constexpr int kAccWave1 = 3;   // one slab per wave, WaveAcc<M>::Pmax objects per step (less LDS)
 constexpr int kMaxWaves = 8;
-[[maybe_unused]] constexpr int kMinWaveForm = 4;   // fewest waves the wave form is used with
+[[maybe_unused]] constexpr int kMinWaveForm = 6;   // fewest waves the wave form is used with
+
+constexpr int kMaxList = 4096;     // noted close calls per wave, at most
+// ... and at least, where the choice of waves allows it: a quarter of the 977
+// objects of a wave at n = 2e6
+[[maybe_unused]] constexpr int kMinList = 256;
+
+// Operands of the split products for M features: 32-feature chunks, of which
+// the last one (R features) takes one, two or three products.
+template <int M>
+struct Split {
+    static constexpr int KC = (M + 31) / 32, R = M - 32 * (KC - 1);
+    static constexpr int kForm = R <= 8 ? 1 : R <= 16 ? 2 : 3;        // products of the last chunk
+    static constexpr int kA = 2 * (KC - 1) + (kForm == 3 ? 2 : 1);    // A operands per block
+    static constexpr int kB = 2 * (KC - 1) + (kForm == 1 ? 1 : 2);    // B operands per column
+    // additions per score on the matrix core: the products, the |c|^2 seed
+    static constexpr int kAdds = 96 * (KC - 1) + 32 * kForm + 2;
+    // dropped split terms, relative to |a b|, in units of 2^-16
+    static constexpr float kDrop = (KC > 1 || kForm == 3) ? 3.02f : 2.01f;
+};
+__host__ __device__ inline int a_operands(int M)
+{
+    const int KC = (M + 31) / 32, R = M - 32 * (KC - 1);
+    return 2 * (KC - 1) + (R <= 16 ? 1 : 2);
+}
 
 // LDS carve-up of a workgroup (dynamic shared memory).
 struct MfmaLds {
-    size_t abf, cnorm, misc, tiles, offs, slab, total;
+    size_t abf, cnorm, misc, tiles, offs, slab, list, total;
     int tile_floats;
+    int list_cap;       // close calls a wave can note
 };
 
 __host__ __device__ inline size_t al16(size_t v) { return (v + 15) & ~size_t(15); }
 
-// Objects added per accumulation step of a wave form (WaveAcc<M, P>::P).
 // Slabs per wave of a wave form.
 __host__ __device__ inline int wave_acc_p(int M, int acc)
 {
@@ -111,24 +148,45 @@ __host__ __device__ constexpr int ring_row(int M) { return (M + 1) | 1; }
 // pairs of blocks; the padding centres score +inf).
 __host__ __device__ inline int centre_blocks(int K) { return ((K + 15) / 16 + 1) / 2 * 2; }
 
+// Tile slot of a wave (floats): the 64 objects and the slack of TileGeom; at
+// least the 128 objects that a wave whose list overflowed gathers there.
+__host__ __device__ constexpr int tile_slot(int M)
+{
+    const int s = (kWave * M + (M > 4 ? M : 4) + 3) / 4 * 4;
+    return s > 2 * kWave ? s : 2 * kWave;
+}
+
 __host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc)
 {
-    const int KC = (M + 31) / 32, KT = centre_blocks(K);
+    const int KT = centre_blocks(K);
     MfmaLds L{};
-    L.tile_floats = (kWave * M + (M > 4 ? M : 4) + 3) / 4 * 4;    // TileGeom<M>::kSlot
+    L.tile_floats = tile_slot(M);
     size_t o = 0;
-    L.abf = o;     o = al16(o + (size_t)KT * KC * kWave * 32);
+    L.abf = o;     o = al16(o + (size_t)KT * a_operands(M) * kWave * 16);
     L.cnorm = o;   o = al16(o + (size_t)KT * 16 * 4);
     L.misc = o;    o = al16(o + 16);
     L.tiles = o;   o = al16(o + (size_t)W * L.tile_floats * 4);
     if (acc == kAccWave || acc == kAccWave1) {
+        // one row more than there are clusters takes the adds of close calls
         L.offs = o;    o = al16(o + (size_t)W * kWave * 4);
-        L.slab = o;    o = al16(o + (size_t)W * wave_acc_p(M, acc) * K * (M + 1) * 8);
+        L.slab = o;    o = al16(o + (size_t)W * wave_acc_p(M, acc) * (K + 1) * (M + 1) * 8);
     } else if (acc == kAccRing) {
         L.slab = o;    o = al16(o + (size_t)K * ring_row(M) * 8);
     }
-    L.total = o;
+    L.list = o;
+    const size_t left = o < (size_t)kMaxLds ? (size_t)kMaxLds - o : 0;
+    const size_t cap = left / ((size_t)W * 8) / 2 * 2;
+    L.list_cap = cap > (size_t)kMaxList ? kMaxList : (int)cap;
+    L.total = o + (size_t)W * L.list_cap * 8;
     return L;
+}
+
+// Orders this wave's LDS accesses of different types (the hardware keeps a
+// wave's LDS accesses in order by itself).
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // Turns of the ring form. The counter in LDS holds the number of turns taken
@@ -167,9 +225,9 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                   int force64)
 {
     using TG = TileGeom<M>;
-    constexpr int KS = (M + 3) / 4;          // 4-feature steps of the fp32 products
-    constexpr int KC = (M + 31) / 32;        // 32-feature chunks of the bf16 products
-    constexpr int kSlot = TG::kSlot;
+    using SP = Split<M>;
+    constexpr int KC = SP::KC, kA = SP::kA, kB = SP::kB;
+    constexpr int kSlot = tile_slot(M);
     constexpr int V = TG::kVecPerLane;
     constexpr bool kAccum = MODE != kAssign;
     constexpr int kAcc = kAccum ? ACC : 0;
@@ -179,23 +237,26 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     constexpr int kP = kShared ? 1 : WaveAcc<M, PA>::P;  // slabs per wave
     extern __shared__ __align__(16) unsigned char smem[];
     const int W = blockDim.x / kWave;
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave;
     const int tid = threadIdx.x;
     const int KT = centre_blocks(K);       // even
     const int kbits = key_bits(KT);        // index bits of the packed keys
 
-    if (MODE == kAssignAccum && stop_before(ctl, t, fixed)) return;
+    if (MODE != kAccumLabels && stop_before(ctl, t, fixed)) return;
     if (MODE == kAccumLabels && stop_after_assign(ctl, fixed)) return;
 
     const MfmaLds L = mfma_lds(M, K, W, kAcc);
     float *tiles = reinterpret_cast<float *>(smem + L.tiles);
     float *tile = tiles + wave * kSlot;
     int32_t *offs = reinterpret_cast<int32_t *>(smem + L.offs) + wave * kWave;
-    uint32_t *abf = reinterpret_cast<uint32_t *>(smem + L.abf);
+    uint4 *abf = reinterpret_cast<uint4 *>(smem + L.abf);       // [KT][kA][64 lanes]
     float *cnorm = reinterpret_cast<float *>(smem + L.cnorm);
-    float *s_cmax = reinterpret_cast<float *>(smem + L.misc);
-    uint32_t *turn = reinterpret_cast<uint32_t *>(smem + L.misc + 4);
-    double *wslabs = reinterpret_cast<double *>(smem + L.slab) + (size_t)wave * kP * K * (M + 1);
+    uint32_t *turn = reinterpret_cast<uint32_t *>(smem + L.misc);
+    // (object, limit) of the close calls of this wave
+    int2 *list = reinterpret_cast<int2 *>(smem + L.list) + (size_t)wave * L.list_cap;
+    const int lcap = L.list_cap;
+    double *wslabs = reinterpret_cast<double *>(smem + L.slab) + (size_t)wave * kP * (K + 1) * (M + 1);
 
     // The grid works in rounds of G*W wave tiles; in round r, wave w of
     // workgroup b takes tile r*G*W + w*G + b. Rounds whose tiles are all full
@@ -210,97 +271,193 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     const int64_t nr_main = nfull / R;
     const int64_t qw = (int64_t)wave * G + blockIdx.x;   // this wave's tile in round 0
 
-    // the first two tiles' loads go out before the prologue
-    float4 buf[2][V];   // register buffers, selected by compile-time index
-    if (nr_main > 0) load_tile<M>(X, qw, lane, buf[0]);
-    if (nr_main > 1) load_tile<M>(X, R + qw, lane, buf[1]);
+    // the first tile's loads go out before the prologue. One tile ahead is
+    // enough: a tile's distance work (64 centres at least on the default
+    // path) takes longer than a read of HBM, and a second buffer (40
+    // registers at M = 37) spilled.
+    float4 buf[V];
+    if (nr_main > 0) load_tile<M>(X, qw, lane, buf);
 
     // ---- prologue: split A operands (-2C, bf16 hi and lo, in lane order),
-    // centre norms, slabs
-    if (MODE != kAccumLabels) {
-        for (int idx = tid; idx < KT * KC * kWave; idx += blockDim.x) {
-            const int tt = idx / (KC * kWave), qc = (idx / kWave) % KC, l = idx % kWave;
-            const int k = tt * 16 + (l & 15), j0 = 32 * qc + 8 * (l >> 4);
-            float a[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                a[e] = (k < K && j0 + e < M) ? -2.0f * C[(int64_t)k * M + j0 + e] : 0.0f;
-            uint32_t hi[4], lo[4];
-            split_bf16x8(a, hi, lo);
-            uint32_t *dst = abf + (size_t)idx * 8;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                dst[e] = hi[e];
-                dst[4 + e] = lo[e];
-            }
-        }
-    }
-    {
-        constexpr int kSlack = kSlot - kWave * M;     // zeros after each tile
-        for (int i = tid; i < W * kSlack; i += blockDim.x)
-            tiles[(i / kSlack) * kSlot + kWave * M + (i % kSlack)] = 0.f;
-    }
+    // centre norms, slabs. Every load is unconditional (clamped into C), a
+    // batch of table entries in flight at a time: with a branch around each
+    // load the table of 1024 centres took 19 us, half of the launch.
     if (kWaveForm) {
         double *slabs = reinterpret_cast<double *>(smem + L.slab);
-        for (int i = tid; i < W * kP * K * (M + 1); i += blockDim.x) slabs[i] = 0.0;
+        for (int i = tid; i < W * kP * (K + 1) * (M + 1); i += blockDim.x) slabs[i] = 0.0;
     } else if (kAcc == kAccRing) {
         double *slab = reinterpret_cast<double *>(smem + L.slab);
         for (int i = tid; i < K * ring_row(M); i += blockDim.x) slab[i] = 0.0;
         if (tid == 0) *turn = 0u;
     }
-    __syncthreads();
+    {
+        constexpr int kSlack = TG::kSlot - kWave * M;     // zeros after each tile
+        for (int i = tid; i < W * kSlack; i += blockDim.x)
+            tiles[(i / kSlack) * kSlot + kWave * M + (i % kSlack)] = 0.f;
+    }
     if (MODE != kAccumLabels) {
-        // |c_k|^2 in fp32, features in order
-        // padding centres (k >= K) get the largest finite norm: their scores
-        // stay finite (a packed key of an infinite score would be a NaN)
-        for (int k = tid; k < KT * 16; k += blockDim.x) {
-            float nk = FLT_MAX;
-            if (k < K) {
-                nk = 0.f;
+        constexpr int kBatch = 4;
+        const int entries = KT * KC * kWave;
+        for (int i0 = tid; i0 < entries; i0 += kBatch * blockDim.x) {
+            float raw[kBatch][8];
 #pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    const float c = C[(int64_t)k * M + j];
-                    nk = __builtin_fmaf(c, c, nk);
+            for (int u = 0; u < kBatch; ++u) {
+                const int idx = i0 + u * (int)blockDim.x;
+                const int tt = idx / (KC * kWave), qc = (idx / kWave) % KC, lg = (idx >> 4) & 3;
+                const int chunk = qc < KC - 1 || SP::kForm == 3 ? lg : SP::kForm == 2 ? (lg & 1) : 0;
+                const int k = tt * 16 + (idx & 15), j0 = 32 * qc + 8 * chunk;
+                const float *row = C + (int64_t)(k < K ? k : K - 1) * M;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) raw[u][e] = row[j0 + e < M ? j0 + e : M - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int idx = i0 + u * (int)blockDim.x;
+                const int tt = idx / (KC * kWave), qc = (idx / kWave) % KC, lg = (idx >> 4) & 3;
+                const bool last = qc == KC - 1;
+                const int chunk = !last || SP::kForm == 3 ? lg : SP::kForm == 2 ? (lg & 1) : 0;
+                const int k = tt * 16 + (idx & 15), j0 = 32 * qc + 8 * chunk;
+                float a[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) a[e] = (k < K && j0 + e < M) ? -2.0f * raw[u][e] : 0.0f;
+                uint32_t hi[4], lo[4];
+                split_bf16x8(a, hi, lo);
+                if (idx >= entries) continue;
+                uint4 *dst = abf + ((size_t)tt * kA + 2 * qc) * kWave + idx % kWave;
+                if (!last || SP::kForm == 3) {
+                    dst[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+                    dst[kWave] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+                } else {
+                    const bool first = lg < 2;         // hi | lo side by side
+                    dst[0] = make_uint4(first ? hi[0] : lo[0], first ? hi[1] : lo[1],
+                                        first ? hi[2] : lo[2], first ? hi[3] : lo[3]);
                 }
             }
-            cnorm[k] = nk;
         }
-        __syncthreads();
-        if (wave == 0) {
-            float m = 0.f;
-            for (int k = lane; k < K; k += kWave) m = fmaxf(m, cnorm[k]);
-            for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-            if (lane == 0) *s_cmax = m;
+        // |c_k|^2 in fp32, features in order; padding centres (k >= K) get
+        // the largest finite norm: their scores stay finite (a packed key of an
+        // infinite score would be a NaN)
+        for (int k = tid; k < KT * 16; k += blockDim.x) {
+            const float *row = C + (int64_t)(k < K ? k : K - 1) * M;
+            float nk = 0.f;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const float c = row[j];
+                nk = __builtin_fmaf(c, c, nk);
+            }
+            cnorm[k] = k < K ? nk : FLT_MAX;
         }
-        __syncthreads();
     }
-    const float cmax = (MODE != kAccumLabels) ? *s_cmax : 0.f;
-    // fp32 error bound of a pass-2 score, relative to (3|c|^2 + |x|^2): 4 KS
-    // products and 4 KS + 2 additions on the matrix core, each rounded
-    // faithfully (within 2^-23 relative, in any order and direction), and the
-    // fp32 |c|^2 (M fused multiply-adds, 2^-24 each, against 3|c|^2); twice
-    // that (two scores) with margins
-    constexpr float kGuard = 2.02f * 1.01f * ((float)(4 * KS + 3) + (float)M / 6.0f) * 1.1920929e-07f;
-
+    __syncthreads();
+    // the largest centre norm, in every wave
+    float cmax = 0.f;
+    if (MODE != kAccumLabels) {
+        for (int k = lane; k < K; k += kWave) cmax = fmaxf(cmax, cnorm[k]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, off, kWave));
+    }
     const int g = lane >> 4, l16 = lane & 15;
-    int nfallback = 0;
-    int nrerun = 0;     // wave tiles that needed the fp32 pass
+    int ncl = 0;             // close calls of this wave
     uint32_t ring_seq = 0;   // steps taken (ring form)
     bool ring_ok = true;     // every turn wait of this wave succeeded
 
-    // One wave tile: stage it in LDS, put the loads of the tile two strides
-    // ahead in flight in the same registers, assign, accumulate.
+    // B operands of the wave's tile: lane (g, l16) holds, for every 16-object
+    // column c, features 32q + 8g .. 32q + 8g + 7 of object 16c + l16 split
+    // into bf16 hi and lo; a last chunk of at most 16 features repeats its
+    // features 8(g & 1) .. in both halves, one of at most 8 in all four lane
+    // groups (hi in the even ones, lo in the odd ones). Past M the A operands
+    // are zero, so the B values there only need to be finite: with M >= 16 the
+    // tile's zero slack covers the last row's reads past M and the rows are
+    // read straight through (the next object's features), else the reads are
+    // clamped to the row.
+    auto b_column = [&](const float *row, uint32_t (&bop)[kB][4]) {
+        constexpr bool kClampReads = M < 16;
+#pragma unroll
+        for (int qc = 0; qc < KC; ++qc) {
+            const bool last = qc == KC - 1;
+            const int chunk = !last || SP::kForm == 3 ? g : SP::kForm == 2 ? (g & 1) : 0;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int f = 32 * qc + 8 * chunk + e;
+                v[e] = kClampReads ? row[f < M ? f : M - 1] : row[f];
+            }
+            uint32_t hi[4], lo[4];
+            split_bf16x8(v, hi, lo);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (last && SP::kForm == 1) {
+                    bop[2 * qc][e] = (g & 1) ? lo[e] : hi[e];
+                } else {
+                    bop[2 * qc][e] = hi[e];
+                    bop[2 * qc + (kB > 1 ? 1 : 0)][e] = lo[e];
+                }
+            }
+        }
+    };
+    auto b_operands = [&](uint32_t (&bop)[kCols][kB][4]) {
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) b_column(tile + (16 * c + l16) * M, bop[c]);
+    };
+    struct Ops {
+        uint32_t a[kA][4];
+        f4v c0;
+    };
+    auto load_ops = [&](int tt, Ops &o) {
+#pragma unroll
+        for (int q = 0; q < kA; ++q) {
+            const uint4 v = abf[((size_t)tt * kA + q) * kWave + lane];
+            o.a[q][0] = v.x;
+            o.a[q][1] = v.y;
+            o.a[q][2] = v.z;
+            o.a[q][3] = v.w;
+        }
+        o.c0 = *reinterpret_cast<const f4v *>(cnorm + tt * 16 + 4 * g);
+    };
+    // products of a score, on top of |c|^2: per full chunk lo(A) hi(B) +
+    // hi(A) lo(B) + hi(A) hi(B), then the last chunk's
+    auto each_product = [&](auto &&product) {
+#pragma unroll
+        for (int qc = 0; qc < KC; ++qc) {
+            if (qc < KC - 1 || SP::kForm == 3) product(2 * qc + (kA > 1 ? 1 : 0), 2 * qc);
+            if (qc < KC - 1 || SP::kForm >= 2) product(2 * qc, 2 * qc + (kB > 1 ? 1 : 0));
+            product(2 * qc, 2 * qc);
+        }
+    };
+    // block o against the four columns
+    auto chain = [&](const Ops &o, const uint32_t (&bop)[kCols][kB][4], f4v (&d)[kCols]) {
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) d[c] = o.c0;
+        each_product([&](int qa, int qb) {
+#pragma unroll
+            for (int c = 0; c < kCols; ++c)
+                d[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(o.a[qa]), as_bf8(bop[c][qb]),
+                                                               d[c], 0, 0, 0);
+        });
+    };
+    // two blocks against one column
+    auto chain_pair = [&](const Ops (&o)[2], const uint32_t (&bop)[kB][4], f4v (&d)[2]) {
+        d[0] = o[0].c0;
+        d[1] = o[1].c0;
+        each_product([&](int qa, int qb) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                d[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(o[u].a[qa]), as_bf8(bop[qb]),
+                                                               d[u], 0, 0, 0);
+        });
+    };
+
+    // One wave tile: stage it in LDS, put the loads of the wave's next tile
+    // in flight in the same registers, assign, accumulate.
     // full: a round of the main loop (every wave tile present and full; the
-    // loads two rounds ahead are issued here) rather than the last one
-    auto step = [&](int64_t r, auto bi, auto full) {
+    // loads of the next round are issued here) rather than the last one
+    auto step = [&](int64_t r, auto full) {
         constexpr bool kFullTile = decltype(full)::value;
-        constexpr bool prefetch = kFullTile;
-        float4 (&bb)[V] = buf[decltype(bi)::value];
         const int64_t q = r * R + qw;
         const bool have = kFullTile || q < nq;
-        if (have) store_tile<M>(tile, lane, bb);
+        if (have) store_tile<M>(tile, lane, buf);
         __builtin_amdgcn_wave_barrier();
-        if (prefetch && r + 2 < nr_main) load_tile<M>(X, q + 2 * R, lane, bb);
+        if (kFullTile && r + 1 < nr_main) load_tile<M>(X, q + R, lane, buf);
         const int64_t i = q * kWave + lane;
         const bool valid = kFullTile || (have && i < n);
         int my_lab = -1;
@@ -311,288 +468,135 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                 if (my_lab < 0 || my_lab >= K) my_lab = -1;
             }
         } else if (have) {
-            // Running best / second best / label of the lane's 4 centres of
-            // each column, over the centre blocks; then the four lanes that
-            // hold the same object merged (rows r, r^1, r^2), and lane l keeps
-            // column l / 16, i.e. object l.
-            float b1[kCols], b2[kCols];
-            int lb[kCols];
-            auto reset = [&]() {
-#pragma unroll
-                for (int c = 0; c < kCols; ++c) {
-                    b1[c] = INFINITY;
-                    b2[c] = INFINITY;
-                    lb[c] = 0;
-                }
-            };
-            auto scan = [&](int tt, const f4v (&d)[kCols]) {
-                const int kb = tt * 16 + 4 * g;
-#pragma unroll
-                for (int c = 0; c < kCols; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float sc = d[c][r];
-                        const bool lt = sc < b1[c];
-                        b2[c] = __builtin_amdgcn_fmed3f(b1[c], b2[c], sc);
-                        b1[c] = lt ? sc : b1[c];
-                        lb[c] = lt ? kb + r : lb[c];
-                    }
-            };
-            float mb1, mb2, mx;
-            int ml;
-            auto finish = [&]() {
-#pragma unroll
-                for (int c = 0; c < kCols; ++c) {
-                    merge_rows<16>(b1[c], b2[c], lb[c]);
-                    merge_rows<32>(b1[c], b2[c], lb[c]);
-                }
-                mb1 = b1[0];
-                mb2 = b2[0];
-                ml = lb[0];
-#pragma unroll
-                for (int c = 1; c < kCols; ++c) {
-                    const bool mine = g == c;
-                    mb1 = mine ? b1[c] : mb1;
-                    mb2 = mine ? b2[c] : mb2;
-                    ml = mine ? lb[c] : ml;
-                }
-            };
             // |x|^2 of the lane's own object (row `lane` of the tile), features
             // in order; it enters only the guard bands, whose margins cover its
             // fp32 rounding
-            mx = 0.f;
+            float mx = 0.f;
 #pragma unroll
             for (int j = 0; j < M; ++j) {
                 const float v = tile[lane * M + j];
                 mx = __builtin_fmaf(v, v, mx);
             }
-            // Both passes keep two accumulator sets and two operand sets: the
-            // matrix cores compute one centre block while the vector ALU scans
-            // the previous one and the next block's operands arrive.
-            // Blocks t0 .. t1-1 (an even count).
-            auto blocks = [&](int t0, int t1, auto &oA, auto &oB, auto load_ops, auto chain,
-                              auto scan_fn) {
-                f4v dA[kCols], dB[kCols];
-                load_ops(t0, oA);
-                load_ops(t0 + 1, oB);
-                chain(oA, dA);
-                int tt = t0;
-                for (; tt + 2 < t1; tt += 2) {
-                    load_ops(tt + 2, oA);
-                    chain(oB, dB);
-                    scan_fn(tt, dA);
-                    load_ops(tt + 3, oB);
-                    chain(oA, dA);
-                    scan_fn(tt + 1, dB);
-                }
-                chain(oB, dB);
-                scan_fn(tt, dA);
-                scan_fn(tt + 1, dB);
-            };
-
-            // ---- pass 1: split-precision products on the bf16 matrix cores.
-            // B operands: object 16c + l16, features 32q + 8g .. 32q + 8g + 7,
-            // split into bf16 hi and lo; A likewise (table in LDS, zero past M).
-            // Each centre block is three products per column,
-            // lo(A) hi(B) + hi(A) lo(B) + hi(A) hi(B), on top of |c|^2.
-            // Past M the A operands are zero, so the B values there only need
-            // to be finite: with M >= 16 the tile's zero slack covers the last
-            // row's reads past M and the rows are read straight through (the
-            // next object's features), else the reads are clamped to the row.
-            {
-                constexpr bool kClampReads = M < 16;
-                uint32_t bh[kCols][KC][4], bl[kCols][KC][4];
+            uint32_t bop[kCols][kB][4];
+            b_operands(bop);
+            // Scan with packed keys: a score with its low `bits` bits
+            // replaced by the centre's index within its group of 2^bits
+            // centres, so that min / med3 / min keep the best and second
+            // best keys and the label comes with the best one. Per group
+            // each lane gathers the keys of its own object from the four
+            // lanes that hold its centre rows, and the group folds into
+            // the lane's running (best, second, label).
+            const int gblocks = (1 << kbits) / 16;            // even
+            const uint32_t kmask = ~((1u << kbits) - 1u);
+            float g1 = INFINITY, g2 = INFINITY;
+            int gl = 0;
+            float k1[kCols], k2[kCols];
+            int kt0 = 0;
+            auto scan_key = [&](int tt, const f4v (&d)[kCols]) {
+                // the four index values of the lane's centre rows, shared
+                // by the four columns; one and-or per key, and per column
+                // two (med3, min3) pairs and a min3 for the running second
+                // best
+                const uint32_t i0 = (uint32_t)((tt - kt0) * 16 + 4 * g);
+                const uint32_t iv[4] = {i0, i0 + 1, i0 + 2, i0 + 3};
 #pragma unroll
                 for (int c = 0; c < kCols; ++c) {
-                    const float *row = tile + (16 * c + l16) * M;
+                    float sk[4];
 #pragma unroll
-                    for (int qc = 0; qc < KC; ++qc) {
-                        float v[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const int f = 32 * qc + 8 * g + e;
-                            v[e] = kClampReads ? row[f < M ? f : M - 1] : row[f];
-                        }
-                        split_bf16x8(v, bh[c][qc], bl[c][qc]);
-                    }
+                    for (int r = 0; r < 4; ++r)
+                        sk[r] = __uint_as_float((__float_as_uint(d[c][r]) & kmask) | iv[r]);
+                    const float ma = __builtin_amdgcn_fmed3f(k1[c], sk[0], sk[1]);
+                    const float b1 = fminf(fminf(k1[c], sk[0]), sk[1]);
+                    const float mb = __builtin_amdgcn_fmed3f(b1, sk[2], sk[3]);
+                    k1[c] = fminf(fminf(b1, sk[2]), sk[3]);
+                    k2[c] = fminf(fminf(k2[c], ma), mb);
                 }
-                struct OpsH {
-                    uint32_t ah[KC][4], al[KC][4];
-                    f4v c0;
-                };
-                auto load_h = [&](int tt, OpsH &o) {
+            };
+            Ops oA, oB;
+            for (; kt0 < KT; kt0 += gblocks) {
+                const int kt1 = KT - kt0 < gblocks ? KT : kt0 + gblocks;
 #pragma unroll
-                    for (int qc = 0; qc < KC; ++qc) {
-                        const uint32_t *src = abf + ((size_t)(tt * KC + qc) * kWave + lane) * 8;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            o.ah[qc][e] = src[e];
-                            o.al[qc][e] = src[4 + e];
-                        }
-                    }
-                    o.c0 = *reinterpret_cast<const f4v *>(cnorm + tt * 16 + 4 * g);
-                };
-                auto chain_h = [&](const OpsH &o, f4v (&d)[kCols]) {
-#pragma unroll
-                    for (int c = 0; c < kCols; ++c) d[c] = o.c0;
-#pragma unroll
-                    for (int qc = 0; qc < KC; ++qc) {
-#pragma unroll
-                        for (int c = 0; c < kCols; ++c)
-                            d[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                as_bf8(o.al[qc]), as_bf8(bh[c][qc]), d[c], 0, 0, 0);
-#pragma unroll
-                        for (int c = 0; c < kCols; ++c)
-                            d[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                as_bf8(o.ah[qc]), as_bf8(bl[c][qc]), d[c], 0, 0, 0);
-#pragma unroll
-                        for (int c = 0; c < kCols; ++c)
-                            d[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                as_bf8(o.ah[qc]), as_bf8(bh[c][qc]), d[c], 0, 0, 0);
-                    }
-                };
-                // Scan with packed keys: a score with its low `bits` bits
-                // replaced by the centre's index within its group of 2^bits
-                // centres, so that min / med3 / min keep the best and second
-                // best keys and the label comes with the best one. Per group
-                // each lane gathers the keys of its own object from the four
-                // lanes that hold its centre rows, and the group folds into
-                // the lane's running (best, second, label).
-                const int gblocks = (1 << kbits) / 16;            // even
-                const uint32_t kmask = ~((1u << kbits) - 1u);
-                float g1 = INFINITY, g2 = INFINITY;
-                int gl = 0;
-                float k1[kCols], k2[kCols];
-                int kt0 = 0;
-                auto scan_key = [&](int tt, const f4v (&d)[kCols]) {
-                    // the four index values of the lane's centre rows, shared
-                    // by the four columns; one and-or per key, and per column
-                    // two (med3, min3) pairs and a min3 for the running second
-                    // best
-                    const uint32_t i0 = (uint32_t)((tt - kt0) * 16 + 4 * g);
-                    const uint32_t iv[4] = {i0, i0 + 1, i0 + 2, i0 + 3};
-#pragma unroll
-                    for (int c = 0; c < kCols; ++c) {
-                        float sk[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            sk[r] = __uint_as_float((__float_as_uint(d[c][r]) & kmask) | iv[r]);
-                        const float ma = __builtin_amdgcn_fmed3f(k1[c], sk[0], sk[1]);
-                        const float b1 = fminf(fminf(k1[c], sk[0]), sk[1]);
-                        const float mb = __builtin_amdgcn_fmed3f(b1, sk[2], sk[3]);
-                        k1[c] = fminf(fminf(b1, sk[2]), sk[3]);
-                        k2[c] = fminf(fminf(k2[c], ma), mb);
-                    }
-                };
-                OpsH oA, oB;
-                for (; kt0 < KT; kt0 += gblocks) {
-                    const int kt1 = KT - kt0 < gblocks ? KT : kt0 + gblocks;
-#pragma unroll
-                    for (int c = 0; c < kCols; ++c) {
-                        k1[c] = INFINITY;
-                        k2[c] = INFINITY;
-                    }
-                    blocks(kt0, kt1, oA, oB, load_h, chain_h, scan_key);
-                    float b1, b2;
-                    own_column_keys(k1, k2, lane, b1, b2);
-                    const int lab = kt0 * 16 + (int)(__float_as_uint(b1) & ~kmask);
-                    const bool take = b1 < g1;
-                    g2 = second_of(g1, g2, b1, b2);
-                    g1 = take ? b1 : g1;
-                    gl = take ? lab : gl;
+                for (int c = 0; c < kCols; ++c) {
+                    k1[c] = INFINITY;
+                    k2[c] = INFINITY;
                 }
-                mb1 = g1;
-                mb2 = g2;
-                ml = gl;
+                // blocks kt0 .. kt1-1 (an even count), two accumulator sets
+                // and two operand sets: the matrix cores compute one block
+                // while the vector ALU scans the previous one and the next
+                // block's operands arrive
+                f4v dA[kCols], dB[kCols];
+                load_ops(kt0, oA);
+                load_ops(kt0 + 1, oB);
+                chain(oA, bop, dA);
+                int tt = kt0;
+                for (; tt + 2 < kt1; tt += 2) {
+                    load_ops(tt + 2, oA);
+                    chain(oB, bop, dB);
+                    scan_key(tt, dA);
+                    load_ops(tt + 3, oB);
+                    chain(oA, bop, dA);
+                    scan_key(tt + 1, dB);
+                }
+                chain(oB, bop, dB);
+                scan_key(tt, dA);
+                scan_key(tt + 1, dB);
+                float b1, b2;
+                own_column_keys(k1, k2, lane, b1, b2);
+                const int lab = kt0 * 16 + (int)(__float_as_uint(b1) & ~kmask);
+                const bool take = b1 < g1;
+                g2 = second_of(g1, g2, b1, b2);
+                g1 = take ? b1 : g1;
+                gl = take ? lab : gl;
             }
-            // Error of a pass-1 score against the exact score |c|^2 - 2 x.c:
-            // with a = ah + al + ea, b = bh + bl + eb (|ea| <= 2^-16 |a|, |al|
+            // Error of a score against the exact score |c|^2 - 2 x.c: with
+            // a = ah + al + ea, b = bh + bl + eb (|ea| <= 2^-16 |a|, |al|
             // <= 2^-8 (1 + 2^-8) |a|, likewise b) the dropped terms
             // (a - ea) eb + al bl + ea b are below 3.02 * 2^-16 |a b| per
-            // feature; the products are exact in fp32 and their sums with |c|^2
-            // take at most 96 KC + 2 roundings on the matrix core, each assumed
-            // only faithful (within 2^-23 relative, any order or direction), so
-            // they add (96 KC + 2) 2^-23 of the terms' magnitudes; |c|^2 in fp32
+            // feature (2.01 * 2^-16 in a chunk that forms al bl too); the
+            // products are exact in fp32 and their sums with |c|^2 take at
+            // most kAdds roundings on the matrix core, each assumed only
+            // faithful (within 2^-23 relative, any order or direction), so
+            // they add kAdds 2^-23 of the terms' magnitudes; |c|^2 in fp32
             // adds M 2^-24 |c|^2. With 2|c_j x_j| <= c_j^2 + x_j^2 each score is
-            // within E (|x|^2 + 3|c|^2), E = 3.02 * 2^-16 + 1.01 (96 KC + 2 + M/6) 2^-23.
+            // within E (|x|^2 + 3|c|^2), E = kDrop 2^-16 + 1.01 (kAdds + M/6) 2^-23.
             // A packed key moves its score by less than 2^(bits - 23) of the
             // score's magnitude, itself below (1 + E)(|x|^2 + 3|c|^2). So the
             // label stands when the two best keys differ by more than twice
-            // E + 1.01 * 2^(bits - 23) (with margins).
+            // E + 1.01 * 2^(bits - 23) (with margins); and a centre whose
+            // score is above the best key by more than that is not the
+            // nearest one.
             const float key_rel = __uint_as_float((uint32_t)(127 - 23 + kbits) << 23);   // 2^(bits-23)
-            const float e1 = 3.02f * 1.5258789e-05f +
-                             1.01f * ((float)(96 * KC + 2) + (float)M / 6.0f) * 1.1920929e-07f +
+            const float e1 = SP::kDrop * 1.5258789e-05f +
+                             1.01f * ((float)SP::kAdds + (float)M / 6.0f) * 1.1920929e-07f +
                              1.01f * key_rel;
-            const float thr1 = 2.02f * e1 * (3.02f * cmax + 1.0001f * mx) + 1e-30f;
-            bool ok = !force64 && ((K == 1) || (mb2 - mb1 > thr1));
-
-            // ---- pass 2 (tiles with a call too close for pass 1): the fp32
-            // products, A = -2C read from C, B = X^T from the tile.
-            if (!force64 && __ballot(valid && !ok) != 0) {
-                float bop[kCols][KS];
-#pragma unroll
-                for (int c = 0; c < kCols; ++c) {
-                    const float *row = tile + (16 * c + l16) * M + g;
-#pragma unroll
-                    for (int s = 0; s < KS; ++s) {
-                        float v = row[4 * s];
-                        if ((M % 4) != 0 && s == KS - 1 && 4 * s + g >= M) v = 0.f;
-                        bop[c][s] = v;
-                    }
-                }
-                struct Ops {
-                    float a[KS];
-                    f4v c0;
-                };
-                auto load_ops = [&](int tt, Ops &o) {
-                    const int k = tt * 16 + l16;
-#pragma unroll
-                    for (int s = 0; s < KS; ++s) {
-                        const int j = 4 * s + g;
-                        o.a[s] = (k < K && j < M) ? -2.0f * C[(int64_t)k * M + j] : 0.0f;
-                    }
-                    o.c0 = *reinterpret_cast<const f4v *>(cnorm + tt * 16 + 4 * g);
-                };
-                auto chain = [&](const Ops &o, f4v (&d)[kCols]) {
-#pragma unroll
-                    for (int c = 0; c < kCols; ++c) d[c] = o.c0;
-#pragma unroll
-                    for (int s = 0; s < KS; ++s)
-#pragma unroll
-                        for (int c = 0; c < kCols; ++c)
-                            d[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.a[s], bop[c][s], d[c], 0, 0, 0);
-                };
-                Ops oA, oB;
-                reset();
-                blocks(0, KT, oA, oB, load_ops, chain, scan);
-                finish();
-                const float thr = kGuard * (3.02f * cmax + 1.0001f * mx) + 1e-30f;
-                ok = (K == 1) || (mb2 - mb1 > thr);
-                if (ctl != nullptr && lane == 0) ++nrerun;
-            }
+            const float thr = 2.02f * e1 * (3.02f * cmax + 1.0001f * mx) + 1e-30f;
+            const bool ok = !force64 && ((K == 1) || (g2 - g1 > thr));
             // a padding centre (index >= K, |c|^2 = FLT_MAX) wins only when
             // every real score overflows; keep such a label in range
-            ml = ml < K ? ml : K - 1;
-            float dmin = 0.f;
-            if (valid && !ok) {
-                double bd;
-                ml = argmin_fp64<M>(tile + lane * M, C, K, bd);
-                dmin = (float)bd;
-            } else if (valid && MODE == kAssign && min_d2 != nullptr) {
-                const float *c = C + (int64_t)ml * M;
-                float d = 0.f;
-#pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    const float e = tile[lane * M + j] - c[j];
-                    d = __builtin_fmaf(e, e, d);
-                }
-                dmin = d;
+            const int ml = gl < K ? gl : K - 1;
+            const bool close = valid && !ok;
+            const uint64_t cm = __ballot(close);
+            if (cm != 0ull) {
+                const int pos = ncl + (int)__builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(cm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0u));
+                if (close && pos < lcap) list[pos] = make_int2((int)i, __float_as_int(g1 + thr));
+                ncl += (int)__popcll(cm);
             }
-            if (ctl != nullptr) nfallback += __popcll(__ballot(valid && !ok));
             if (valid) {
-                labels[i] = ml;
-                if (MODE == kAssign && min_d2 != nullptr) min_d2[i] = dmin;
-                my_lab = ml;
+                labels[i] = close ? -1 : ml;
+                if (MODE == kAssign && min_d2 != nullptr && !close) {
+                    const float *c = C + (int64_t)ml * M;
+                    float d = 0.f;
+#pragma unroll
+                    for (int j = 0; j < M; ++j) {
+                        const float e = tile[lane * M + j] - c[j];
+                        d = __builtin_fmaf(e, e, d);
+                    }
+                    min_d2[i] = d;
+                }
+                // a close call's features go to the spare row of the wave
+                // forms and, in the ring form, nowhere
+                my_lab = !close ? ml : kWaveForm ? K : -1;
             }
         }
 
@@ -600,7 +604,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
             // (labels read back may be out of range even in a full tile)
             if (have)
                 accumulate_tile<M, PA, kFullTile && MODE != kAccumLabels, kShared>(
-                    valid ? my_lab : -1, tile, offs, wslabs, K, lane);
+                    valid ? my_lab : -1, tile, offs, wslabs, K + 1, lane);
         } else if (kAcc == kAccRing) {
             // This wave's turn of the step (every wave takes it, with or
             // without objects): lane l adds object l's features and count to
@@ -627,27 +631,329 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
         }
     };
 
-    // The register buffers alternate between rounds. Every wave of a
-    // workgroup runs the same steps (the ring form needs every wave's turn in
-    // every step).
-    for (int64_t r = 0; r < nr_main; r += 2) {
-        step(r, std::integral_constant<int, 0>{}, std::true_type{});
-        if (r + 1 < nr_main) step(r + 1, std::integral_constant<int, 1>{}, std::true_type{});
-    }
+    // Every wave of a workgroup runs the same steps (the ring form needs every
+    // wave's turn in every step).
+    for (int64_t r = 0; r < nr_main; ++r) step(r, std::true_type{});
     if (nr_main * R < nq) {
         const int64_t q = nr_main * R + qw;
-        if (q < nfull) load_tile<M>(X, q, lane, buf[0]);
-        else if (q < nq) load_tail_tile<M>(X, n, q, lane, buf[0]);
-        step(nr_main, std::integral_constant<int, 0>{}, std::false_type{});
+        if (q < nfull) load_tile<M>(X, q, lane, buf);
+        else if (q < nq) load_tail_tile<M>(X, n, q, lane, buf);
+        step(nr_main, std::false_type{});
     }
 
-    if (ctl != nullptr && lane == 0 && nfallback > 0) atomicAdd(&ctl->fallbacks, nfallback);
-    if (ctl != nullptr && lane == 0 && nrerun > 0) atomicAdd(&ctl->reruns, nrerun);
+    // ---- the close calls
+    auto load_row = [&](int i, float (&x)[M]) {
+        const float *xr = X + (int64_t)i * M;
+#pragma unroll
+        for (int j = 0; j + 4 <= M; j += 4) {
+            const f4u v = *reinterpret_cast<const f4u *>(xr + j);
+            x[j] = v[0];
+            x[j + 1] = v[1];
+            x[j + 2] = v[2];
+            x[j + 3] = v[3];
+        }
+#pragma unroll
+        for (int j = M / 4 * 4; j < M; ++j) x[j] = xr[j];
+    };
+    // label of the lane's object x (open lanes) by the direct form over all
+    // centres: each fp32 distance is within gamma_{M+1} of the exact one, and
+    // fp64 over all centres decides where that leaves it open
+    auto direct = [&](const float (&x)[M], bool open) -> int {
+        constexpr float kTau = 4.0f * (float)(M + 2) * 5.9604645e-8f;
+        float b1 = INFINITY, b2 = INFINITY;
+        int ld = 0;
+        if (!force64)
+            for (int k = 0; k < K; ++k) {
+                float d = 0.f;
+#pragma unroll
+                for (int j = 0; j < M; ++j) {
+                    const float e = x[j] - C[k * M + j];
+                    d = __builtin_fmaf(e, e, d);
+                }
+                const bool lt = d < b1;
+                b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
+                b1 = lt ? d : b1;
+                ld = lt ? k : ld;
+            }
+        const bool sure = !force64 && ((K == 1) || (b2 - b1 > kTau * b2 && b2 >= 1e-30f));
+        if (open && !sure) {
+            double bd;
+            ld = argmin_fp64<M>(x, C, K, bd);
+        }
+        return ld;
+    };
+    auto store_label = [&](const float (&x)[M], int i, int lab, int mark) {
+        labels[i] = lab ^ mark;
+        if (MODE == kAssign && min_d2 != nullptr)
+            min_d2[i] = (float)dist_fp64<M>(x, C + (int64_t)lab * M);
+    };
+    int first[kMaxWaves + 1];      // list position of each wave's first object
+    first[0] = 0;
+    int total = 0;                 // objects in the lists
+    uint32_t over = 0;             // waves whose list overflowed
+    // place of list position p: in the list of the last wave that starts at
+    // or before it
+    auto entry = [&](int p) -> int2 * {
+        int w = 0, base = 0;
+#pragma unroll
+        for (int v = 1; v < kMaxWaves; ++v)
+            if (p >= first[v]) {
+                w = v;
+                base = first[v];
+            }
+        return reinterpret_cast<int2 *>(smem + L.list) + (size_t)w * lcap + (p - base);
+    };
+    if (MODE != kAccumLabels) {
+        // The close calls of the workgroup's waves, one list after the other,
+        // in columns of 16 objects dealt to the waves in turn (a wave alone
+        // rarely has many, and a column costs a quarter of a tile or more).
+        // The four lanes (g, l16) of an object hold its features and find the
+        // candidates among their own centre rows.
+        int *wcount = reinterpret_cast<int *>(tiles);
+        __syncthreads();
+        if (lane == 0) wcount[wave * kSlot] = ncl;
+        __syncthreads();
+        int all = 0, batches = 0;
+#pragma unroll
+        for (int w = 0; w < kMaxWaves; ++w) {
+            const int c = w < W ? wcount[w * kSlot] : 0;
+            all += c;
+            if (c > lcap) {
+                batches += (c + kWave - 1) / kWave;
+                over |= 1u << w;
+            }
+            first[w + 1] = first[w] + (c <= lcap ? c : 0);
+        }
+        total = __builtin_amdgcn_readfirstlane(first[kMaxWaves]);
+        over = __builtin_amdgcn_readfirstlane(over);
+        __syncthreads();               // the slots may be used again
+        const int columns = (total + 15) / 16;
+        batches += columns;
+        // one add per workgroup: adds of 2048 waves to one word take 20 us
+        if (ctl != nullptr && tid == 0 && all > 0) {
+            atomicAdd(&ctl->fallbacks, all);
+            atomicAdd(&ctl->reruns, batches);
+        }
+        for (int col = wave; col < columns; col += W) {
+            const int p = 16 * col + l16;
+            const bool act = p < total;
+            const int2 e = *entry(act ? p : 16 * col);
+            const int i = e.x;
+            const float lim = act ? __int_as_float(e.y) : -INFINITY;
+            float x[M];
+            load_row(i, x);
+            int lab = 0;
+            bool open = act;
+            if (!force64) {
+                wave_sync();
+                if (g == 0)
+#pragma unroll
+                    for (int j = 0; j < M; ++j) tile[l16 * M + j] = x[j];
+                wave_sync();
+                uint32_t bop[kB][4];
+                b_column(tile + l16 * M, bop);
+                // up to four candidates of this lane, 16 bits each
+                uint64_t cand = 0;
+                int nc = 0;
+                Ops o[2], nx[2];
+                load_ops(0, nx[0]);
+                load_ops(1, nx[1]);
+                for (int tt = 0; tt < KT; tt += 2) {
+                    o[0] = nx[0];
+                    o[1] = nx[1];
+                    const int tn = tt + 2 < KT ? tt + 2 : tt;
+                    load_ops(tn, nx[0]);
+                    load_ops(tn + 1, nx[1]);
+                    f4v d[2];
+                    chain_pair(o, bop, d);
+                    // a NaN score (which the sum keeps) or limit makes the
+                    // centre a candidate
+                    const float lo = fminf(fminf(fminf(d[0][0], d[0][1]), fminf(d[0][2], d[0][3])),
+                                           fminf(fminf(d[1][0], d[1][1]), fminf(d[1][2], d[1][3])));
+                    const float sum = ((d[0][0] + d[0][1]) + (d[0][2] + d[0][3])) +
+                                      ((d[1][0] + d[1][1]) + (d[1][2] + d[1][3]));
+                    if (__ballot(!(lo > lim) || sum != sum) == 0ull) continue;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int k = (tt + u) * 16 + 4 * g + r;
+                            const bool in = !(d[u][r] > lim) && k < K;
+                            cand = in ? (cand << 16) | (uint64_t)k : cand;
+                            nc += in ? 1 : 0;
+                        }
+                }
+                double bd = INFINITY;
+                for (int u = 0; u < (nc < 4 ? nc : 4); ++u) {
+                    const int k = (int)((cand >> (16 * u)) & 0xffffu);
+                    const double dk = dist_fp64<M>(x, C + (int64_t)k * M);
+                    if (dk < bd || (dk == bd && dk < INFINITY && k < lab)) {
+                        bd = dk;
+                        lab = k;
+                    }
+                }
+                int most = nc, some = nc;
+#pragma unroll
+                for (int m = 16; m <= 32; m <<= 1) {
+                    const double od = __shfl_xor(bd, m, kWave);
+                    const int ol = __shfl_xor(lab, m, kWave);
+                    if (od < bd || (od == bd && ol < lab)) {
+                        bd = od;
+                        lab = ol;
+                    }
+                    const int om = __shfl_xor(most, m, kWave);
+                    most = om > most ? om : most;
+                    some += __shfl_xor(some, m, kWave);
+                }
+                open = act && (most > 4 || some == 0);
+            }
+            if (__ballot(open) != 0ull) {
+                const int ld = direct(x, open);
+                lab = open ? ld : lab;
+            }
+            if (act && g == 0) store_label(x, i, lab, 0);
+            if (kAcc != 0) {
+                // lane (g, l16) adds features g, g + 4, ... of its object, to
+                // the wave's first slab or, in the column's turn, to the
+                // workgroup's
+                const uint32_t want = ring_seq * (uint32_t)W + (uint32_t)col;
+                if (kAcc == kAccRing && ring_ok) ring_ok = ring_wait(turn, want);
+                if (act) {
+                    double *row = kWaveForm
+                        ? wslabs + (size_t)lab * (M + 1)
+                        : reinterpret_cast<double *>(smem + L.slab) + (int64_t)lab * ring_row(M);
+#pragma unroll
+                    for (int j = 0; j < M; j += 4) {
+                        float a0 = x[j], a1 = x[j + 1 < M ? j + 1 : j];
+                        float a2 = x[j + 2 < M ? j + 2 : j], a3 = x[j + 3 < M ? j + 3 : j];
+                        asm("" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3));   // values, not addresses
+                        const float v01 = (g & 1) ? a1 : a0, v23 = (g & 1) ? a3 : a2;
+                        const float v = g < 2 ? v01 : v23;
+                        if (j + 4 <= M || j + g < M)
+                            __hip_atomic_fetch_add(row + j + g, (double)v, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    if (g == 0)
+                        __hip_atomic_fetch_add(row + M, 1.0, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                if (kAcc == kAccRing) ring_pass(turn, want + 1);
+            }
+        }
+        // A list that overflowed is not used: its wave's tiles are read again
+        // for marked labels, through a buffer of 128 objects (the list's
+        // place, or the idle tile slot).
+        if (ncl > lcap) {
+            if (lcap < kWave) wave_sync();
+            int *sbuf = lcap >= kWave ? reinterpret_cast<int *>(list) : reinterpret_cast<int *>(tile);
+            int have = 0;
+            int64_t q = qw;
+            for (;;) {
+                while (have < kWave && q < nq) {
+                    const int64_t i = q * kWave + lane;
+                    const bool mark = i < n && labels[i] < 0;
+                    const uint64_t mm = __ballot(mark);
+                    const int pos = have + (int)__builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u));
+                    if (mark) sbuf[pos] = (int)i;
+                    have += (int)__popcll(mm);
+                    q += R;
+                }
+                wave_sync();
+                if (have == 0) break;
+                const int m = have < kWave ? have : kWave;
+                have -= m;
+                const bool act = lane < m;
+                const int i = sbuf[have + (act ? lane : 0)];
+                wave_sync();
+                float x[M];
+                load_row(i, x);
+                const int lab = direct(x, act);
+                // in the ring form the label keeps its mark until the sums below
+                if (act) {
+                    store_label(x, i, lab, kAcc == kAccRing ? -1 : 0);
+                    if (kWaveForm) {
+                        // one lane per object: the LDS applies the lanes of
+                        // an add in a fixed order
+                        double *row = wslabs + (size_t)lab * (M + 1);
+#pragma unroll
+                        for (int j = 0; j < M; ++j)
+                            __hip_atomic_fetch_add(row + j, (double)x[j], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
+                        __hip_atomic_fetch_add(row + M, 1.0, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    }
+                }
+            }
+        }
+    }
+    if (kAcc == kAccRing && MODE != kAccumLabels && over != 0) {
+        // The sums of the marked objects of the waves whose list overflowed, in
+        // a fixed order: waves ascending, their tiles ascending, lanes
+        // ascending. Each wave adds its own share of the features of all of
+        // them (the count goes with feature 0), so that no sum is shared
+        // between waves.
+        constexpr int RS = ring_row(M);
+        constexpr int kPer = (M + kMaxWaves - 1) / kMaxWaves;   // features at a time
+        constexpr int kAhead = 4;                               // batches in flight
+        double *slab = reinterpret_cast<double *>(smem + L.slab);
+        const int j0 = M * wave / W, j1 = M * (wave + 1) / W;
+        // batch: kAhead x 64 objects i with labels lab (-1: none)
+        auto add_batch = [&](const int64_t (&i)[kAhead], const int (&lab)[kAhead]) {
+            for (int jc = j0; jc < j1; jc += kPer) {
+                float v[kAhead][kPer];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int j = 0; j < kPer; ++j)
+                        v[u][j] = X[i[u] * M + (jc + j < j1 ? jc + j : j0)];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+                    if (lab[u] >= 0) {
+                        double *row = slab + (int64_t)lab[u] * RS;
+#pragma unroll
+                        for (int j = 0; j < kPer; ++j)
+                            if (jc + j < j1)
+                                __hip_atomic_fetch_add(row + jc + j, (double)v[u][j],
+                                                       __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (jc == 0)
+                            __hip_atomic_fetch_add(row + M, 1.0, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+            }
+        };
+        __syncthreads();                           // every object is decided
+        for (int w = 0; w < W; ++w) {
+            if (((over >> w) & 1u) == 0u) continue;
+            for (int64_t q = (int64_t)w * G + blockIdx.x; q < nq; q += kAhead * R) {
+                int64_t i[kAhead];
+                int lab[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int64_t iu = (q + u * R) * kWave + lane;
+                    i[u] = iu < n ? iu : 0;
+                    lab[u] = iu < n ? ~labels[iu] : -1;
+                }
+                add_batch(i, lab);
+            }
+        }
+        __syncthreads();                           // every mark has been read
+        if (ncl > lcap)
+            for (int64_t q = qw; q < nq; q += R) {
+                const int64_t i = q * kWave + lane;
+                if (i < n) {
+                    const int v = labels[i];
+                    if (v < 0) labels[i] = ~v;
+                }
+            }
+    }
+
     if (kAcc == kAccRing && ctl != nullptr && lane == 0 && !ring_ok) atomicAdd(&ctl->ring_stalls, 1);
 
     if (kWaveForm) {
         __syncthreads();
-        write_wave_partials<M, PA, kShared>(reinterpret_cast<const double *>(smem + L.slab), W, K,
+        write_wave_partials<M, PA, kShared>(reinterpret_cast<const double *>(smem + L.slab), W, K, K + 1,
                                part_sums + (int64_t)blockIdx.x * K * M,
                                part_counts + blockIdx.x, gridDim.x);
     } else if (kAcc == kAccRing) {
@@ -702,10 +1008,17 @@ using LaunchFn = hipError_t (*)(const StepArgs &, Mode, const AccumPlan &, hipSt
 constexpr int kPartLo = LLOYD_PART * kMaxM / LLOYD_PARTS + 1;
 constexpr int kPartN = kMaxM / LLOYD_PARTS;
 
+template <int M>
+constexpr LaunchFn entry()
+{
+    if constexpr (!lloyd_built(M)) return nullptr;
+    else return &launch_m<M>;
+}
+
 template <int... Is>
 constexpr auto make_table(std::integer_sequence<int, Is...>)
 {
-    return std::array<LaunchFn, sizeof...(Is)>{&launch_m<kPartLo + Is>...};
+    return std::array<LaunchFn, sizeof...(Is)>{entry<kPartLo + Is>()...};
 }
 
 }  // namespace
@@ -714,39 +1027,52 @@ hipError_t LLOYD_PART_FN(launch_tile_part)(const StepArgs &a, Mode mode, const A
 {
     static constexpr auto table = make_table(std::make_integer_sequence<int, kPartN>{});
     if (a.M < kPartLo || a.M >= kPartLo + kPartN) return hipErrorInvalidValue;
-    return table[a.M - kPartLo](a, mode, plan, s);
+    const LaunchFn fn = table[a.M - kPartLo];
+    return fn ? fn(a, mode, plan, s) : hipErrorInvalidValue;
 }
 
 #if LLOYD_PART == 0
+namespace {
+
+// Most waves of a workgroup whose state fits in LDS with a list of kMinList
+// each, or one wave with what is left (0: not even one fits).
+int most_waves(int M, int K, int acc)
+{
+    for (int w = kMaxWaves; w > 0; --w) {
+        const MfmaLds L = mfma_lds(M, K, w, acc);
+        if (L.total <= (size_t)kMaxLds && (w == 1 || L.list_cap >= kMinList)) return w;
+    }
+    return 0;
+}
+
+// Accumulation form and waves of an accumulating launch: private slabs (the
+// most objects per step that leaves the most waves) while at least
+// kMinWaveForm waves fit, else one shared slab, which leaves more waves.
+int accum_form(int M, int K, int &waves)
+{
+    const int w_p = most_waves(M, K, kAccWave), w_1 = most_waves(M, K, kAccWave1);
+    if (w_p >= kMinWaveForm && w_p >= w_1) {
+        waves = w_p;
+        return kAccWave;
+    }
+    if (w_1 >= kMinWaveForm) {
+        waves = w_1;
+        return kAccWave1;
+    }
+    waves = most_waves(M, K, kAccRing);
+    return kAccRing;
+}
+
+}  // namespace
+
 AccumPlan plan_tile(int64_t n, int M, int K, Mode mode)
 {
     AccumPlan p{};
     p.path = kPathTile;
     const int64_t nq = (n + kWave - 1) / kWave;
-    auto fits = [&](int W, int acc) { return mfma_lds(M, K, W, acc).total <= (size_t)kMaxLds; };
-    auto most_waves = [&](int acc) {      // 0 when not even one wave fits
-        int w = kMaxWaves;
-        while (w > 0 && !fits(w, acc)) --w;
-        return w;
-    };
     int W = kMaxWaves, acc = 0;
-    if (mode == kAssign) {
-        W = most_waves(0);
-    } else {
-        // private slabs (the most objects per step that leaves the most waves)
-        // while at least kMinWaveForm waves fit, else one shared slab
-        const int w_p = most_waves(kAccWave), w_1 = most_waves(kAccWave1);
-        if (w_p >= kMinWaveForm && w_p >= w_1) {
-            acc = kAccWave;
-            W = w_p;
-        } else if (w_1 >= kMinWaveForm) {
-            acc = kAccWave1;
-            W = w_1;
-        } else {
-            acc = kAccRing;
-            W = most_waves(kAccRing);
-        }
-    }
+    if (mode == kAssign) W = most_waves(M, K, 0);
+    else acc = accum_form(M, K, W);
     // no more waves than there are 64-object tiles
     while (W > 1 && W / 2 >= nq) W /= 2;
     int64_t groups = (nq + W - 1) / W;
@@ -758,14 +1084,28 @@ AccumPlan plan_tile(int64_t n, int M, int K, Mode mode)
     return p;
 }
 
+// The shapes that a forced matrix-core path takes: centre operands of two
+// 16-byte parts per 32 features and lane, one tile and the workgroup slab in
+// one workgroup's LDS (an upper bound of what the launches need).
 bool tile_fits(int M, int K)
 {
-    return mfma_lds(M, K, 1, kAccRing).total <= (size_t)kMaxLds;
+    const size_t table = (size_t)centre_blocks(K) * ((M + 31) / 32) * kWave * 32;
+    const size_t norms = al16((size_t)centre_blocks(K) * 16 * 4) + 16;
+    const size_t tile = al16((size_t)((kWave * M + (M > 4 ? M : 4) + 3) / 4 * 4) * 4);
+    return al16(table + norms + tile) + al16((size_t)K * ring_row(M) * 8) <= (size_t)kMaxLds;
+}
+
+int tile_waves(int M, int K, Mode mode)
+{
+    int W = 0;
+    if (mode == kAssign) W = most_waves(M, K, 0);
+    else accum_form(M, K, W);
+    return W;
 }
 
 hipError_t launch_tile(const StepArgs &a, Mode mode, const AccumPlan &plan, hipStream_t s)
 {
-    if (a.M < 1 || a.M > kMaxM) return hipErrorInvalidValue;
+    if (a.M < 1 || a.M > kMaxM || plan.waves < 1) return hipErrorInvalidValue;
     switch ((a.M - 1) / (kMaxM / LLOYD_PARTS)) {
 #define LLOYD_CASE(P) case P: return launch_tile_part_##P(a, mode, plan, s);
         LLOYD_PART_CASES
