@@ -32,6 +32,7 @@ UNIT_FLAGS = {"lloyd_lane_mfma.hip": ["-mllvm", "-amdgpu-sched-strategy=iterativ
 PARTS = 4
 SOURCES = ([("kmeans_api.hip", [], "kmeans_api.o"), ("lloyd_ctl.hip", [], "lloyd_ctl.o"),
             ("lloyd_centres.hip", [], "lloyd_centres.o"), ("farthest.hip", [], "farthest.o"),
+            ("lloyd_accum.hip", [], "lloyd_accum.o"),
             ("diameter.hip", [], "diameter.o"), ("lloyd_l1.hip", UNIT_FLAGS["lloyd_l1.hip"], "lloyd_l1.o")]
            + [(f, [f"-DLLOYD_PART={p}", *UNIT_FLAGS.get(f, [])], f.replace(".hip", f"_part{p}.o"))
               for f in ("lloyd_tile.hip", "lloyd_lane.hip", "lloyd_lane_mfma.hip")
@@ -76,7 +77,7 @@ def build(verbose: bool = True, jobs: int = 8, incremental: bool = False) -> str
             ot = os.path.getmtime(obj)
             if ot > os.path.getmtime(os.path.join(CSRC, src)) and ot > head_t:
                 continue
-        cmd = [hipcc(), *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc(), *HIPCC_FLAGS, *extra, *os.environ.get("KMEANS_HIPCC_EXTRA", "").split(), "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
         while sum(p.poll() is None for _, p in procs) >= jobs:
             time.sleep(0.05)

@@ -56,6 +56,21 @@ int select_path(int32_t M, int32_t K, uint32_t flags)
     return (K > 16 && tile) ? kPathTile : kPathValu;
 }
 
+// Whether the default path of a shape with many centres assigns and sums in two
+// launches: the fused tile kernel holds the centre operands and the K x M fp64
+// sums in LDS, and with fewer than five waves beside them (K = 384, M = 32: one;
+// K = 1024, M = 16: none) the SIMDs idle, while the assigning launch alone
+// keeps its waves. n = 262147, M = 16, K = 1024: 2,926 us per iteration on the
+// vector ALU, the only path that fitted.
+constexpr int kMinFusedWaves = 5;
+
+bool use_split(int32_t M, int32_t K, uint32_t flags)
+{
+    if (flags & (KMEANS_PATH_DIRECT | KMEANS_PATH_MFMA | KMEANS_PATH_TILES)) return false;
+    if (K <= 16 || lane_mfma_fits(M, K)) return false;
+    return tile_waves(M, K, kAssignAccum) < kMinFusedWaves && tile_waves(M, K, kAssign) >= 2;
+}
+
 AccumPlan plan_for(int p, int64_t n, int32_t M, int32_t K, Mode mode)
 {
     if (p == kPathTile) return plan_tile(n, M, K, mode);
@@ -67,6 +82,8 @@ hipError_t launch_step(const StepArgs &a, Mode mode, const AccumPlan &plan, hipS
 {
     if (plan.path == kPathTile) return launch_tile(a, mode, plan, s);
     if (plan.path == kPathLaneMfma) return launch_lane_mfma(a, mode, plan, s);
+    if (plan.path == kPathSplit)
+        return mode == kAccumLabels ? launch_accum(a, plan, s) : hipErrorInvalidValue;
     return launch_lane(a, mode, plan, s);
 }
 
@@ -111,11 +128,22 @@ Layout layout(int64_t n, int32_t M, int32_t K, uint32_t flags)
         L.l1_fused = f.waves > 0;
         if (L.l1_fused) L.plan = f;
     }
-    if (!L.l1_fused) L.plan = plan_for(select_path(M, K, flags), n, M, K, kAssignAccum);
     const size_t km = (size_t)K * M;
-    L.sums_off = align_up(sizeof(Ctl), 256);
-    L.counts_off = align_up(L.sums_off + (size_t)L.plan.groups * km * sizeof(double), 256);
-    L.total = align_up(L.counts_off + (size_t)L.plan.groups * K * sizeof(int32_t), 256);
+    auto sized = [&](const AccumPlan &plan) {
+        L.sums_off = align_up(sizeof(Ctl), 256);
+        L.counts_off = align_up(L.sums_off + (size_t)plan.groups * km * sizeof(double), 256);
+        return align_up(L.counts_off + (size_t)plan.groups * K * sizeof(int32_t), 256);
+    };
+    if (!L.l1_fused) L.plan = plan_for(select_path(M, K, flags), n, M, K, kAssignAccum);
+    L.total = sized(L.plan);
+    if (!L.l1_fused && use_split(M, K, flags)) {
+        // two launches per iteration need fewer partial rows; the size that
+        // callers see (and that decides what fits the static workspace) stays
+        // the fused launch's
+        L.plan = plan_accum(n, M, K);
+        const size_t need = sized(L.plan);
+        if (need > L.total) L.total = need;
+    }
     return L;
 }
 
@@ -235,6 +263,8 @@ int run_impl(const float *X, int64_t n, int32_t M, int32_t K, const float *init_
     const bool l1 = (flags & KMEANS_METRIC_L1) != 0;
     const L1Plan p1 = l1 && !L.l1_fused ? plan_l1(n, M, K) : L1Plan{};
     if (l1 && !L.l1_fused && p1.waves < 1) return KMEANS_EUNSUPPORTED;
+    const AccumPlan split =
+        L.plan.path == kPathSplit ? plan_tile(n, M, K, kAssign) : AccumPlan{};
     const int every = timing == nullptr ? 0 : (timing->sample_every > 0 ? timing->sample_every : 16);
     // events: one before the first launch, one after the last, and a pair
     // stamped with the start and end of each sampled assigning launch
@@ -310,6 +340,11 @@ int run_impl(const float *X, int64_t n, int32_t M, int32_t K, const float *init_
                 rc = hip_status(launch_l1(a, p1, s));
                 a.ev_start = a.ev_stop = nullptr;
                 if (!rc) rc = hip_status(launch_step(a, kAccumLabels, L.plan, s));
+            } else if (L.plan.path == kPathSplit) {
+                // assign, then the sums of Eq. (1) from those labels
+                rc = hip_status(launch_tile(a, kAssign, split, s));
+                a.ev_start = a.ev_stop = nullptr;
+                if (!rc) rc = hip_status(launch_accum(a, L.plan, s));
             } else {
                 rc = hip_status(launch_step(a, kAssignAccum, L.plan, s));
                 a.ev_start = a.ev_stop = nullptr;
@@ -500,7 +535,8 @@ int kmeans_assign(const float *X, int64_t n, int32_t M, const float *centers, in
         return hip_status(launch_l1(a, p1, s));
     }
     if (select_path(M, K, flags) < 0) return KMEANS_EUNSUPPORTED;
-    const AccumPlan plan = plan_for(select_path(M, K, flags), n, M, K, kAssign);
+    const int path = use_split(M, K, flags) ? kPathTile : select_path(M, K, flags);
+    const AccumPlan plan = plan_for(path, n, M, K, kAssign);
     return hip_status(launch_step(a, kAssign, plan, s));
 }
 
