@@ -27,16 +27,13 @@
 //      second-best key of each object block over the centre blocks, and two
 //      rounds of row swaps (v_permlane32_swap, then v_permlane16_swap) leave
 //      lane l with the two best keys of object l; a label is accepted when the
-//      two differ by more than twice the proven error bound thr/2. Otherwise
-//      (a close call) the keys of the object's column are formed again from
-//      the same split operands, every centre whose key is within thr of the
-//      best becomes a candidate (no other centre can be the nearest), and the
-//      object is decided among its candidates with fp64 distances in the
-//      reference operation order (lowest index on ties): one close object at
-//      a time, its features made wave-uniform, lane k computing the distance
-//      to centre k from an LDS copy of the centres, so that no memory read
-//      of the close path waits behind the next tile's loads. Every label is
-//      the exact-arithmetic argmin;
+//      two differ by more than twice the proven error bound thr/2. The others
+//      (close calls) are noted in a list in LDS and decided after the wave's
+//      last tile, 64 at a time, one object per lane: direct-form fp32 distances
+//      to every centre, whose error is relative to the distance itself
+//      (gamma_{M+1}) and not to the norms, and fp64 distances in the reference
+//      operation order (lowest index on ties) where those leave a gap below
+//      4 gamma_{M+2}. Every label is the exact-arithmetic argmin;
 //   5. accumulation (the numerator and denominator of Eq. (1)): lane l
 //      writes the slab row offset of object l to the wave's offset table;
 //      lanes (h, .) read the offsets of their 32 objects back with broadcast
@@ -74,12 +71,12 @@
 // range). |x|^2 here sums the squares of every value the lane group read,
 // including the up to seven floats past the object's M features: an upper
 // bound, which only widens the band (and makes an object whose neighbour holds
-// an infinity or a NaN go to the fp64 path). The same bound makes a close
-// call's candidate set complete: a centre whose key exceeds the best key b1 by
-// more than thr has an exact score above b1 + thr - e >= b1 + e (e the error
-// bound of one key, thr >= 2.02 e), while the best key's centre scores at most
-// b1 + e; the 1 % margin keeps that gap far above fp64 rounding, so the fp64
-// distances order the candidates as they order all centres.
+// an infinity or a NaN go to the fp64 path).
+//
+// Why the close calls wait: decided inside the step, one object at a time, they
+// took 360 of 459 us of an assignment with a third of its objects close (n = 2e6,
+// M = 25, K = 64, random initial centres), and their code in the loop cost the
+// launches without any close call 2 %.
 #include "lloyd.h"
 #include "lloyd_device.h"
 
@@ -107,6 +104,12 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 // later (whose lines have by then left the cache).
 constexpr int kWaves = 8;
 constexpr int kMinWavesPerSimd = 2;   // caps registers at 256 per lane
+// An assignment holds no accumulation values: four waves per SIMD with one
+// block (two workgroups of eight waves on a compute unit), three with more
+// (three workgroups of four waves; at four 94 registers spilled).
+__host__ __device__ constexpr int assign_waves_per_simd(int KB) { return KB == 1 ? 4 : 3; }
+__host__ __device__ constexpr int assign_waves(int KB) { return KB == 1 ? 8 : 4; }
+__host__ __device__ constexpr int assign_groups(int KB) { return KB == 1 ? 2 : 3; }   // per compute unit
 constexpr int kMaxMLane = 32;         // features: four lane groups of eight
 [[maybe_unused]] constexpr int kMaxKLane = 64;   // centres: up to four 16-row A operands
 
@@ -123,27 +126,46 @@ __host__ __device__ constexpr int lane_slabs(int KB) { return KB == 4 ? 1 : 2; }
 // instead of in registers.
 __host__ __device__ constexpr bool lane_a_in_lds(int KB) { return KB > 1; }
 
-// LDS of a workgroup: with accumulation [W][S][K][M] fp64 slabs, [W][K] int32
-// counts and [W][64] int32 slab offsets of the objects of the current tile
+// LDS of a workgroup: with accumulation [W][S][K + 1][M] fp64 slabs and
+// [W][K + 1] int32 counts (the last row and count take the adds of close
+// calls) and [W][64] int32 slab offsets of the objects of the current tile
 // (rounded up to 16 bytes); with distances, the A table [3][KB][64] x 16 bytes
-// when there is more than one block, then the centres [K][M] in fp32 (one copy
-// per wave with one block, which needs no workgroup barrier, else one for the
-// workgroup; read by the fp64 decisions of close calls).
+// when there is more than one block; in assignments the centres [K][M] in fp32
+// (for the distances that may be asked for); then a list of close calls per
+// wave (object indices) in what is left of the launch's share.
 [[maybe_unused]] __host__ __device__ inline size_t lane_acc_bytes(int M, int K, int W)
 {
     const int S = lane_slabs(lane_blocks(K));
-    return ((size_t)W * S * K * M * 8 + (size_t)W * K * 4 + (size_t)W * kWave * 4 + 15) & ~size_t(15);
+    return ((size_t)W * S * (K + 1) * M * 8 + (size_t)W * (K + 1) * 4 + (size_t)W * kWave * 4 + 15) &
+           ~size_t(15);
 }
 [[maybe_unused]] __host__ __device__ inline size_t lane_tab_bytes(int K, Mode mode)
 {
     const int KB = lane_blocks(K);
     return (mode != kAccumLabels && lane_a_in_lds(KB)) ? (size_t)3 * KB * kWave * 16 : 0;
 }
-[[maybe_unused]] __host__ __device__ inline size_t lane_lds_bytes(int M, int K, int W, Mode mode)
+[[maybe_unused]] __host__ __device__ inline size_t lane_fixed_bytes(int M, int K, int W, Mode mode)
 {
     const size_t acc = mode == kAssign ? 0 : lane_acc_bytes(M, K, W);
-    const size_t ctab = mode != kAccumLabels ? (size_t)(lane_blocks(K) == 1 ? W : 1) * K * M * 4 : 0;
+    const size_t ctab = mode == kAssign ? ((size_t)K * M * 4 + 15) & ~size_t(15) : 0;
     return acc + lane_tab_bytes(K, mode) + ctab;
+}
+// Close calls a wave can note: what LDS leaves (in an assignment its share of
+// the workgroups of a compute unit), at most kMaxList.
+constexpr size_t kStaticLds = 64;       // the waves' counts
+constexpr int kMaxList = 2048;
+[[maybe_unused]] __host__ __device__ inline int lane_list_cap(int M, int K, int W, Mode mode)
+{
+    if (mode == kAccumLabels) return 0;
+    const size_t all =
+        mode == kAssign ? kMaxLds / assign_groups(lane_blocks(K)) - kStaticLds : kMaxLds - kStaticLds;
+    const size_t used = lane_fixed_bytes(M, K, W, mode);
+    const size_t cap = used < all ? (all - used) / ((size_t)W * 4) / 4 * 4 : 0;
+    return cap > (size_t)kMaxList ? kMaxList : (int)cap;
+}
+[[maybe_unused]] __host__ __device__ inline size_t lane_lds_bytes(int M, int K, int W, Mode mode)
+{
+    return lane_fixed_bytes(M, K, W, mode) + (size_t)W * lane_list_cap(M, K, W, mode) * 4;
 }
 
 // Object rows after the last row of a tile that the operand loads may touch
@@ -229,18 +251,8 @@ __host__ __device__ constexpr bool lane_a_in_lds(int KB) { return KB > 1; }
     return m0 + m1;
 }
 
-// Bitwise or of x over the four lanes l16 + 16g (g = 0..3), in each of them:
-// a row swap returns, in every lane, the values of both lanes of its pair.
-[[maybe_unused]] __device__ inline uint32_t or_rows(uint32_t x)
-{
-    const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    x = a[0] | a[1];
-    const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    return b[0] | b[1];
-}
-
 template <int M, int MODE, int KB>
-__global__ void __launch_bounds__(kWaves * kWave, kMinWavesPerSimd)
+__global__ void __launch_bounds__(kWaves * kWave, MODE == kAssign ? assign_waves_per_simd(KB) : kMinWavesPerSimd)
 lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict__ C, int K,
                  int32_t *__restrict__ labels, const int32_t *__restrict__ labels_in,
                  float *__restrict__ min_d2, double *__restrict__ part_sums,
@@ -255,8 +267,9 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     constexpr int kBits = key_bits_of(KB);     // index bits of a packed key
     // With more than one block the operand loads of the next tile go into the
     // registers of the current one once it is split (one register set), which
-    // leaves room for the A operands of the other blocks.
-    constexpr bool kOneOpSet = KB > 1;
+    // leaves room for the A operands of the other blocks. (An assignment has
+    // no accumulation values, and may need the tile for its distances.)
+    constexpr bool kOneOpSet = KB > 1 && MODE != kAssign;
     // With four blocks a tile's distance work is long enough to cover a read
     // that hits the cache: the accumulation values of a tile are loaded at the
     // start of its own step, before the next tile's operand loads (so waiting
@@ -274,14 +287,15 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     if (MODE == kAssignAccum && stop_before(ctl, t, fixed)) return;
     if (MODE == kAccumLabels && stop_after_assign(ctl, fixed)) return;
 
-    double *slabs = reinterpret_cast<double *>(smem) + (size_t)wave * S * K * M;
+    const int KR = K + 1;                         // slab rows
+    double *slabs = reinterpret_cast<double *>(smem) + (size_t)wave * S * KR * M;
     int32_t *cnts = reinterpret_cast<int32_t *>(reinterpret_cast<double *>(smem) +
-                                                (size_t)W * S * K * M) + wave * K;
+                                                (size_t)W * S * KR * M) + wave * KR;
     int32_t *offs = reinterpret_cast<int32_t *>(reinterpret_cast<double *>(smem) +
-                                                (size_t)W * S * K * M) + W * K + wave * kWave;
+                                                (size_t)W * S * KR * M) + W * KR + wave * kWave;
     if (kAcc) {
-        for (int i = lane; i < S * K * M; i += kWave) slabs[i] = 0.0;
-        for (int i = lane; i < K; i += kWave) cnts[i] = 0;
+        for (int i = lane; i < S * KR * M; i += kWave) slabs[i] = 0.0;
+        for (int i = lane; i < KR; i += kWave) cnts[i] = 0;
     }
 
     // A operands for the whole launch: for block cb, lane (g, o) holds
@@ -303,8 +317,9 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
             const int ko = 16 * cb + o16;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
+                // unconditional (clamped): zeroed below
                 const int f = 8 * g + e;
-                craw[cb][e] = (ko < K && f < M) ? C[ko * M + f] : 0.f;
+                craw[cb][e] = C[(ko < K ? ko : K - 1) * M + (f < M ? f : M - 1)];
             }
         }
     }
@@ -370,13 +385,16 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         if (kDist) load_ops(q, xb[0]);
         if (kAcc && !kLateAcc) load_acc(q, xa[0], std::false_type{});
     }
+    __builtin_amdgcn_sched_barrier(0);     // issued here, not where they are first used
 
-    // the A table in LDS: [hi | lo | seeds][KB][64 lanes], 16 bytes each; then
-    // the centres, [K][M] fp32 (the wave's own copy with one block)
-    uint4 *atab = reinterpret_cast<uint4 *>(smem + (kAcc ? lane_acc_bytes(M, K, W) : 0));
-    float *ctab_w = reinterpret_cast<float *>(smem + (kAcc ? lane_acc_bytes(M, K, W) : 0) +
-                                              lane_tab_bytes(K, (Mode)MODE)) +
-                    (kALds ? 0 : wave * K * M);
+    // the A table in LDS: [hi | lo | seeds][KB][64 lanes], 16 bytes each; the
+    // centres of an assignment, [K][M] fp32; the wave's list of close calls
+    unsigned char *after = smem + (kAcc ? lane_acc_bytes(M, K, W) : 0);
+    uint4 *atab = reinterpret_cast<uint4 *>(after);
+    float *ctab = reinterpret_cast<float *>(after + lane_tab_bytes(K, (Mode)MODE));
+    const int lcap = lane_list_cap(M, K, W, (Mode)MODE);
+    int32_t *lists = reinterpret_cast<int32_t *>(smem + lane_fixed_bytes(M, K, W, (Mode)MODE));
+    int32_t *list = lists + (size_t)wave * lcap;
     if (kDist) {
 #pragma unroll
         for (int cb = 0; cb < KB; ++cb) {
@@ -384,6 +402,7 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
             float nrm = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
+                craw[cb][e] = (16 * cb + o16 < K && 8 * g + e < M) ? craw[cb][e] : 0.f;
                 a[e] = -2.0f * craw[cb][e];
                 nrm = __builtin_fmaf(craw[cb][e], craw[cb][e], nrm);
             }
@@ -398,11 +417,11 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
                 cseed[cb][r] = k < K ? nk : FLT_MAX;
                 if (k < K) cmax = fmaxf(cmax, nk);
             }
-            if (!kALds || wave == 0) {
+            if (MODE == kAssign && wave == 0) {
                 const int ko = 16 * cb + o16;
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    if (ko < K && 8 * g + e < M) ctab_w[ko * M + 8 * g + e] = craw[cb][e];
+                    if (ko < K && 8 * g + e < M) ctab[ko * M + 8 * g + e] = craw[cb][e];
             }
             if (kALds && wave == 0) {
                 atab[(0 * KB + cb) * kWave + lane] = make_uint4(ah[cb][0], ah[cb][1], ah[cb][2], ah[cb][3]);
@@ -414,10 +433,8 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         }
         cmax = fmaxf(cmax, __shfl_xor(cmax, 16, kWave));
         cmax = fmaxf(cmax, __shfl_xor(cmax, 32, kWave));
-        // the tables are read by other lanes (and, for the shared ones, other
-        // waves) from here on
-        if (kALds) __syncthreads();
-        else __builtin_amdgcn_wave_barrier();
+        // the tables are read by other waves from here on
+        if (kALds || MODE == kAssign) __syncthreads();
     }
     // block cb's operands and seeds: registers, or the LDS table
     auto a_ops = [&](int cb, uint32_t (&h4)[4], uint32_t (&l4)[4], f4v &seed) {
@@ -445,7 +462,7 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     constexpr uint32_t kIdxMask = (1u << kBits) - 1u;
     constexpr uint32_t kKeyMask = ~kIdxMask;
 
-    int nfallback = 0;
+    int ncl = 0;             // close calls of this wave
 
     // One tile (kTail: the guarded loads and validity tests): xb / xa hold its
     // operand and accumulation values (loaded one tile earlier); the loads of
@@ -531,158 +548,35 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
             lab = lab < K ? lab : K - 1;
             const float thr = 2.02f * kE * (3.02f * cmax + 1.0001f * xsq) + 1e-30f;
             const bool ok = !force64 && ((K == 1) || (b2 - b1 > thr));
-            float dmin = 0.f;
             const bool close = valid && !ok;
             const uint64_t cmask = __ballot(close);
             if (cmask != 0ull) {
-                if (force64) {
-                    if (valid) {
-                        double bd;
-                        lab = argmin_fp64<M>(X + i * M, C, K, bd);
-                        dmin = (float)bd;
+                const int pos = ncl + (int)__builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(cmask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cmask, 0u));
+                if (close && pos < lcap) list[pos] = (int32_t)i;
+                ncl += (int)__popcll(cmask);
+            }
+            if (MODE == kAssign && min_d2 != nullptr) {
+                // |x - c|^2 in the operand layout: lane (g, o) adds its
+                // features of object 16b + o, the object's four lanes then
+                // their sums
+                float dd[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const float *c = ctab + __shfl(lab, 16 * b + o16, kWave) * M + 8 * g;
+                    float acc = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float v = xb[b][e / 4][e % 4] - c[8 * g + e < M ? e : 0];
+                        if (8 * g + e < M) acc = __builtin_fmaf(v, v, acc);
                     }
-                } else {
-                    // Close calls: only centres whose key is within thr of the
-                    // best key can be the nearest (a key errs by at most half
-                    // of thr, so any other centre's exact score exceeds the
-                    // best centre's). For each column that holds a close call
-                    // the keys are formed again exactly as above from the same
-                    // split operands, each lane marks its candidates for the
-                    // object of the column, and the four lanes of an object
-                    // combine their marks; then the objects are decided one at
-                    // a time with fp64 distances (below).
-                    const float lim_own = close ? b1 + thr : -INFINITY;
-                    // the limits of the four lanes o16 + 16b (b = 0..3) in
-                    // every lane: a 32-lane swap leaves rows r and r + 2 in
-                    // the lanes of rows r and r + 2 (r = 0, 1), two 16-lane
-                    // swaps then rows 0 and 1, and rows 2 and 3
-                    float lim4[4];
-                    {
-                        float lo = lim_own, hi = lim_own;
-                        swap32(lo, hi);
-                        float r0 = lo, r1 = lo, r2 = hi, r3 = hi;
-                        swap16(r0, r1);
-                        swap16(r2, r3);
-                        lim4[0] = r0;
-                        lim4[1] = r1;
-                        lim4[2] = r2;
-                        lim4[3] = r3;
-                    }
-                    uint32_t clo = 0u, chi = 0u;
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        if (((cmask >> (16 * b)) & 0xffffull) == 0ull) continue;   // uniform
-                        const float lim = lim4[b];
-                        uint32_t mlo = 0u, mhi = 0u;
-#pragma unroll
-                        for (int cb = 0; cb < KB; ++cb) {
-                            uint32_t h4[4], l4[4];
-                            f4v d;
-                            a_ops(cb, h4, l4, d);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(l4), as_bf8(bh[b]), d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(h4), as_bf8(bl[b]), d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(h4), as_bf8(bh[b]), d, 0, 0, 0);
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const uint32_t idx = i0 + (uint32_t)(16 * cb + r);
-                                const float key =
-                                    __uint_as_float((__float_as_uint(d[r]) & kKeyMask) | idx);
-                                // bit idx - i0 of the word (an immediate), shifted by
-                                // i0 below; a centre is ruled out only by a key
-                                // above the limit, so a NaN key (a score that
-                                // overflowed, or values read past the object's
-                                // features that hold an infinity or a NaN) or a NaN
-                                // limit keeps every such centre a candidate
-                                const uint32_t bit = !(key > lim) ? 1u << (16 * (cb & 1) + r) : 0u;
-                                if (cb < 2) mlo |= bit;
-                                else mhi |= bit;
-                            }
-                        }
-                        mlo <<= i0;
-                        mhi <<= i0;
-                        // lane l16 + 16b keeps the marks of its own object
-                        mlo = or_rows(mlo);
-                        if (KB == 4) mhi = or_rows(mhi);
-                        clo = g == b ? mlo : clo;
-                        chi = g == b ? mhi : chi;
-                    }
-                    if (K < 32) clo &= (1u << K) - 1u;      // padding centres never count
-                    if (K > 32 && K < 64) chi &= (1u << (K - 32)) - 1u;
-                    // The fp64 decisions, one close object at a time: its
-                    // features are made wave-uniform (scalars), lane k
-                    // computes the distance to centre k if that is one of the
-                    // object's candidates (the fp64 sum in the reference
-                    // order), and a butterfly over the lanes keeps the
-                    // smallest distance, the lowest index on ties. A distance
-                    // that is not below infinity (overflow, NaN) never wins,
-                    // and with no finite distance the label is 0: what the
-                    // ascending scan with a strict comparison gives.
-                    uint64_t rem = cmask;
-                    while (rem != 0ull) {
-                        const int l = (int)__builtin_ctzll(rem);     // uniform
-                        rem &= rem - 1ull;
-                        float xr[M];
-                        if constexpr (kAcc) {
-                            // the tile's accumulation registers hold the
-                            // object's features (feature f of object l in lane
-                            // 32h + f, register s): the register is picked by
-                            // selects and read out lane by lane, so that no
-                            // memory read waits behind the next tile's loads
-                            const int sl = S == 2 ? (l & 31) : (l >> 1);
-                            const int hl = S == 2 ? (l >> 5) : (l & 1);
-                            float v = xa[0];
-#pragma unroll
-                            for (int u = 1; u < 32; ++u) v = sl == u ? xa[u] : v;
-#pragma unroll
-                            for (int f = 0; f < M; ++f)
-                                xr[f] = __int_as_float(
-                                    __builtin_amdgcn_readlane(__float_as_int(v), 32 * hl + f));
-                        } else {
-                            const float *xs = X + (q * kWave + l) * M;   // uniform address
-#pragma unroll
-                            for (int f = 0; f < M; ++f) xr[f] = xs[f];
-                        }
-                        const uint64_t cand =
-                            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)chi, l) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((int)clo, l);
-                        double dk = INFINITY;
-                        if ((cand >> lane) & 1ull) {
-                            const double dd = dist_fp64<M>(xr, ctab_w + lane * M);
-                            dk = dd < INFINITY ? dd : INFINITY;
-                        }
-                        int kk = lane;
-#pragma unroll
-                        for (int m = 1; m < kWave; m <<= 1) {
-                            const double od = __shfl_xor(dk, m, kWave);
-                            const int ok2 = __shfl_xor(kk, m, kWave);
-                            if (od < dk || (od == dk && ok2 < kk)) {
-                                dk = od;
-                                kk = ok2;
-                            }
-                        }
-                        if (lane == l) {
-                            lab = kk;
-                            dmin = (float)dk;
-                        }
-                    }
+                    dd[b] = acc;
                 }
-                if (ctl != nullptr) nfallback += __popcll(cmask);
+                const float d = own_block_sum(dd);
+                if (valid && !close) min_d2[i] = d;
             }
-            if (MODE == kAssign && min_d2 != nullptr && valid && ok) {
-                const float *xg = X + i * M;
-                const float *c = C + (int64_t)lab * M;
-                float dd = 0.f;
-#pragma unroll
-                for (int f = 0; f < M; ++f) {
-                    const float e = xg[f] - c[f];
-                    dd = __builtin_fmaf(e, e, dd);
-                }
-                dmin = dd;
-            }
-            if (valid) {
-                labels[i] = lab;
-                if (MODE == kAssign && min_d2 != nullptr) min_d2[i] = dmin;
-            }
+            if (valid) labels[i] = close ? -1 : lab;
+            lab = close ? K : lab;             // the spare slab row
         } else {
             lab = valid ? labels_in[i] : -1;
             if (lab >= K) lab = -1;
@@ -692,7 +586,7 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
             // slab row of object `lane`, -1: none; stored where the lanes
             // that add the object read it (entry 32h + s for the object of
             // lane (h, .) in step s)
-            const int my_off = adds ? ((S == 2 ? (lane >> 5) : 0) * K + lab) * M : -1;
+            const int my_off = adds ? ((S == 2 ? (lane >> 5) : 0) * KR + lab) * M : -1;
             const int my_pos = S == 2 ? lane : (lane & 1) * 32 + (lane >> 1);
             if (adds) atomicAdd(cnts + lab, 1);
             // all 32 offsets first (8 broadcast reads), then the adds (each
@@ -739,21 +633,137 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         step(q, xb[0], xa[0], xb[kOpSets - 1], xa[kLateAcc ? 0 : 1], q, std::true_type{});
     }
 
-    if (ctl != nullptr && lane == 0 && nfallback > 0) atomicAdd(&ctl->fallbacks, nfallback);
+    // ---- the close calls: lane l decides object i
+    auto decide = [&](bool act, int i) {
+        const float *xr = X + (int64_t)i * M;
+        float x[M];
+#pragma unroll
+        for (int f = 0; f + 4 <= M; f += 4) {
+            const f4v v = *reinterpret_cast<const f4u *>(xr + f);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[f + e] = v[e];
+        }
+#pragma unroll
+        for (int f = M / 4 * 4; f < M; ++f) x[f] = xr[f];
+        constexpr float kTau = 4.0f * (float)(M + 2) * 5.9604645e-8f;
+        float b1 = INFINITY, b2 = INFINITY;
+        int lab = 0;
+        if (!force64)
+            for (int k = 0; k < K; ++k) {
+                float d = 0.f;
+#pragma unroll
+                for (int f = 0; f < M; ++f) {
+                    const float e = x[f] - C[k * M + f];
+                    d = __builtin_fmaf(e, e, d);
+                }
+                const bool lt = d < b1;
+                b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
+                b1 = lt ? d : b1;
+                lab = lt ? k : lab;
+            }
+        const bool sure = !force64 && ((K == 1) || (b2 - b1 > kTau * b2 && b2 >= 1e-30f));
+        if (act && !sure) {
+            double bd;
+            lab = argmin_fp64<M>(x, C, K, bd);
+        }
+        if (act) {
+            labels[i] = lab;
+            if (MODE == kAssign && min_d2 != nullptr)
+                min_d2[i] = (float)dist_fp64<M>(x, C + (int64_t)lab * M);
+            if (kAcc) {
+                // one lane per object into the wave's slab of the object's
+                // tile half: the LDS applies the lanes of an add in a fixed
+                // order
+                atomicAdd(cnts + lab, 1);
+                const int half = S == 2 ? (i >> 5) & 1 : 0;
+                double *row = slabs + ((size_t)half * KR + lab) * M;
+#pragma unroll
+                for (int f = 0; f < M; ++f)
+                    __hip_atomic_fetch_add(row + f, (double)x[f], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+        }
+    };
+    __shared__ __align__(16) int32_t wcount[kWaves];
+    if (kDist && lane == 0) wcount[wave] = ncl;
+    if (kDist || kAcc) __syncthreads();
+    int counts[kWaves];
+    int all = 0;
+    if (kDist) {
+        *reinterpret_cast<int4 *>(counts) = *reinterpret_cast<const int4 *>(wcount);
+        *reinterpret_cast<int4 *>(counts + 4) = *reinterpret_cast<const int4 *>(wcount + 4);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            counts[w] = w < W ? counts[w] : 0;
+            all += counts[w];
+        }
+        all = __builtin_amdgcn_readfirstlane(all);
+    }
+    // (unlikely: the code below is laid out behind the sums)
+    if (kDist && __builtin_expect(all > 0, 0)) {
+        // The close calls of the workgroup's waves, one list after the other,
+        // in batches of 64 dealt to the waves in turn: a wave alone rarely has
+        // a full batch, and a batch costs the same for one object as for 64.
+        int first[kWaves + 1];
+        first[0] = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) first[w + 1] = first[w] + (counts[w] <= lcap ? counts[w] : 0);
+        const int total = __builtin_amdgcn_readfirstlane(first[kWaves]);
+        // one add per workgroup: adds of 2048 waves to one word take 20 us
+        if (ctl != nullptr && threadIdx.x == 0) atomicAdd(&ctl->fallbacks, all);
+        for (int p0 = wave * kWave; p0 < total; p0 += W * kWave) {
+            const bool act = p0 + lane < total;
+            const int p = act ? p0 + lane : p0;
+            int w = 0, base = 0;
+#pragma unroll
+            for (int v = 1; v < kWaves; ++v)
+                if (p >= first[v]) {
+                    w = v;
+                    base = first[v];
+                }
+            decide(act, lists[(size_t)w * lcap + (p - base)]);
+        }
+        // A list that overflowed is not used: its wave's tiles are read again
+        // for marked labels, through the list's place as a buffer.
+        if (ncl > lcap) {
+            int have = 0;
+            int64_t qq = q0;
+            for (;;) {
+                while (have < kWave && qq < nt) {
+                    const int64_t i = qq * kWave + lane;
+                    const bool mark = i < n && labels[i] < 0;
+                    const uint64_t mm = __ballot(mark);
+                    const int pos = have + (int)__builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u));
+                    if (mark) list[pos] = (int32_t)i;
+                    have += (int)__popcll(mm);
+                    qq += stride;
+                }
+                __builtin_amdgcn_wave_barrier();
+                if (have == 0) break;
+                const int m = have < kWave ? have : kWave;
+                have -= m;
+                const bool act = lane < m;
+                const int i = list[have + (act ? lane : 0)];
+                __builtin_amdgcn_wave_barrier();
+                decide(act, i);
+            }
+        }
+        if (kAcc) __syncthreads();
+    }
 
     if (kAcc) {
-        __syncthreads();
-        const double *all = reinterpret_cast<const double *>(smem);
-        const int32_t *allc = reinterpret_cast<const int32_t *>(all + (size_t)W * S * K * M);
+        const double *allsums = reinterpret_cast<const double *>(smem);
+        const int32_t *allc = reinterpret_cast<const int32_t *>(allsums + (size_t)W * S * KR * M);
         double *ps = part_sums + (int64_t)blockIdx.x * K * M;
         for (int e = threadIdx.x; e < K * M; e += blockDim.x) {
             double s = 0.0;
-            for (int r = 0; r < S * W; ++r) s = s + all[(size_t)r * K * M + e];
+            for (int r = 0; r < S * W; ++r) s = s + allsums[(size_t)r * KR * M + e];
             ps[e] = s;
         }
         for (int k = threadIdx.x; k < K; k += blockDim.x) {
             int32_t c = 0;
-            for (int w = 0; w < W; ++w) c += allc[w * K + k];
+            for (int w = 0; w < W; ++w) c += allc[w * KR + k];
             part_counts[(int64_t)k * gridDim.x + blockIdx.x] = c;
         }
     }
@@ -766,7 +776,9 @@ hipError_t launch_mb(const StepArgs &a, Mode mode, const AccumPlan &p, hipStream
 #define LANE_MFMA_LAUNCH(MD)                                                                   \
     do {                                                                                       \
         auto kern = lane_mfma_kernel<M, MD, KB>;                                               \
-        if (p.lds_bytes > (size_t)kMaxLds) return hipErrorInvalidConfiguration;                \
+        static const size_t st = static_lds_bytes(reinterpret_cast<const void *>(kern));       \
+        if (st > (size_t)kMaxLds || st + p.lds_bytes > (size_t)kMaxLds)                        \
+            return hipErrorInvalidConfiguration;                                               \
         hipExtLaunchKernelGGL(kern, grid, block, p.lds_bytes, s, a.ev_start, a.ev_stop, 0,     \
                               a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,            \
                               a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64);    \
@@ -824,19 +836,22 @@ hipError_t LLOYD_PART_FN(launch_lane_mfma_part)(const StepArgs &a, Mode mode, co
 #if LLOYD_PART == 0
 bool lane_mfma_fits(int M, int K)
 {
-    return K <= kMaxKLane && M <= kMaxMLane &&
-           lane_lds_bytes(M, K, kWaves, kAssignAccum) <= (size_t)kMaxLds;
+    return K <= kMaxKLane && M <= kMaxMLane;   // (the slabs of K = 64, M = 32 leave 470 list places)
 }
 
 AccumPlan plan_lane_mfma(int64_t n, int M, int K, Mode mode)
 {
     AccumPlan p{};
     p.path = kPathLaneMfma;
-    int W = kWaves;
+    const int KB = lane_blocks(K);
+    int W = mode == kAssign ? assign_waves(KB) : kWaves;
     const int64_t nq = (n + kWave - 1) / kWave;
-    while (W > 1 && W / 2 >= nq) W /= 2;
+    // few tiles: one wave per workgroup rather than eight on one compute unit
+    while (W > 1 && (nq + W - 1) / W < kCUs) W /= 2;
     int64_t groups = (nq + W - 1) / W;
-    if (groups > kCUs) groups = kCUs;       // one persistent workgroup per compute unit
+    // persistent workgroups
+    const int64_t most = mode == kAssign ? assign_groups(KB) * kCUs : kCUs;
+    if (groups > most) groups = most;
     p.waves = W;
     p.groups = (int)groups;
     p.accum = 0;

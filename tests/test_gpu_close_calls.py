@@ -1,4 +1,4 @@
-"""Close calls of the 64-object-tile kernel and the two-launch form of large K x M.
+"""Close calls of the matrix-core kernels and the two-launch form of large K x M.
 
 Objects whose split-precision scores leave the label open are noted during a
 launch and decided after its last tile, among the centres within their limit
@@ -52,9 +52,11 @@ def _check(X, C, path):
     assert torch.equal(again[1].view(torch.int32), gC.view(torch.int32))
 
 
-# M at the edges of the product forms; K = 65 ... 256 the fused launch, larger
-# K x M the two-launch form
-SHAPES = [(1, 8, 65), (63, 9, 100), (64, 16, 129), (4_097, 17, 200), (5_001, 24, 257),
+# K <= 64 with M <= 32: one object per lane, with one, two and four centre
+# blocks; otherwise tiles, with M at the edges of the product forms, K = 65 ...
+# 256 the fused launch, larger K x M the two-launch form
+SHAPES = [(1, 3, 5), (65, 10, 8), (5_001, 25, 16), (4_097, 10, 24), (129, 31, 33), (3_001, 32, 64),
+          (1, 8, 65), (63, 9, 100), (64, 16, 129), (4_097, 17, 200), (5_001, 24, 257),
           (4_999, 32, 65), (3_000, 33, 70), (5_003, 40, 20), (2_049, 41, 150), (3_001, 49, 90),
           (2_000, 64, 17), (4_097, 16, 1024), (3_001, 32, 512), (2_003, 64, 256), (4_001, 25, 600),
           (70, 2, 1000)]
@@ -79,6 +81,28 @@ def test_overflowing_lists_follow_the_oracle(n, M, K, path):
     print(f"[overflow] n={n} M={M} K={K}", flush=True)
     X, C = _case(n, M, K, n + M, "offset")
     _check(X, C, path)
+
+
+@pytest.mark.parametrize("with_d2", [False, True])
+def test_overflowing_lists_of_the_lane_kernel(with_d2):
+    """More close calls per wave than the list holds (470 beside the slabs of
+    K = 64, M = 32): the labels equal those of the direct form, whose calls do
+    not go through a list, and the centres to one unit in the last place."""
+    n, M, K = 1_200_003, 32, 64
+    print(f"[overflow lane] n={n} M={M} K={K}", flush=True)
+    X, C = _case(n, M, K, 5, "offset")
+    Xg, Cg = torch.from_numpy(X).to(DEV), torch.from_numpy(C).to(DEV)
+    if with_d2:
+        lab, d2 = km.kmeans_assign(Xg, Cg, with_min_d2=True)
+        want, wd2 = km.kmeans_assign(Xg, Cg, with_min_d2=True, path="direct")
+        assert torch.equal(lab, want)
+        torch.testing.assert_close(d2, wd2, rtol=(M + 2) * 2.0**-22, atol=1e-30)
+        return
+    lab, cen, cnt, _ = km.kmeans_run(Xg, K, Cg, 1, fixed_iters=True)
+    want, wcen, wcnt, _ = km.kmeans_run(Xg, K, Cg, 1, fixed_iters=True, path="direct")
+    assert torch.equal(lab, want) and torch.equal(cnt, wcnt)
+    scale = wcen.abs().amax(1, keepdim=True)
+    assert ((cen - wcen).abs() <= 2.0**-23 * scale).all()
 
 
 @pytest.mark.parametrize("n,M,K", [(1, 16, 1024), (64, 16, 1024), (65, 63, 260), (40_007, 15, 1000),
