@@ -16,7 +16,7 @@ the centres are congruent, "converge_mode"), and, on the same workload, the
 farthest-point initial
 centres of Algorithm 1 step 1 (K passes over X, "init_farthest") and the
 diameter of Eq. (3) with the centre of gravity (Algorithm 2 steps 1-2, two
-passes over all pairs on the bf16 matrix cores, "diameter"), and Lloyd
+passes over all pairs on the fp16 matrix cores, "diameter"), and Lloyd
 iterations that assign by the L1 distance instead ("l1_metric").
 
 python bench.py [--gpus 1] [--steps 1000] [--warmup 20] [--workload 3]
@@ -53,10 +53,10 @@ DTYPE = {"lane-mfma": "bf16x3-split/f32-acc, f64 re-decision", "tiles": "bf16x3-
          "direct": "f32, f64 re-decision"}
 DISTANCE = {
     "lane-mfma": "expanded form on the bf16 matrix cores: operands split into bf16 hi and lo, "
-                 "three products per block, fp32 accumulation; close calls re-decided in fp64",
+                 "three products per block, fp32 accumulation; close calls re-decided in fp32 direct form or fp64",
     "tiles": "expanded form on the bf16 matrix cores: operands split into bf16 hi and lo, "
-             "three products per block, fp32 accumulation; close tiles recomputed with fp32 "
-             "products, the closest calls re-decided in fp64",
+             "up to three products per block, fp32 accumulation; close calls re-decided "
+             "in fp64 among their candidates",
     "direct": "direct form in fp32 on the vector ALU; close calls re-decided in fp64",
 }
 
@@ -201,11 +201,11 @@ def time_init(torch, km, Xg, K, stored, reps=5):
     }
 
 
-BF16_PEAK_TFLOPS = 2500.0       # MI355X dense bf16 matrix peak
+BF16_PEAK_TFLOPS = 2500.0       # MI355X dense bf16 (and fp16) matrix peak
 
 
 def time_diameter(torch, km, Xg, reps=2):
-    """Priced as one screening pass over the n(n-1)/2 pairs: three bf16 matrix
+    """Priced as one screening pass over the n(n-1)/2 pairs: one fp16 matrix
     products over 32 ceil((M+2)/32) features per pair (the second pass only
     revisits the few work items whose maximum reaches the threshold)."""
     n, M = Xg.shape
@@ -222,15 +222,15 @@ def time_diameter(torch, km, Xg, reps=2):
     sec = s.elapsed_time(e) / 1e3 / reps
     P = 32 * ((M + 2 + 31) // 32)
     pairs = n * (n - 1) // 2
-    flops = pairs * 3 * 2 * P
+    flops = pairs * 2 * P
     return {
         "ms": round(sec * 1e3, 2),
         "d2": float(d2.item()),
         "pair": [int(v) for v in pair.cpu().numpy()],
         "repeatable": bool(d2.item() == d2a.item() and torch.equal(pair, paira)),
         "pairs_per_s": round(pairs / sec, 1),
-        "bf16_matrix_TFLOPs": round(flops / sec / 1e12, 1),
-        "frac_bf16_peak": round(flops / sec / 1e12 / BF16_PEAK_TFLOPS, 4),
+        "fp16_matrix_TFLOPs": round(flops / sec / 1e12, 1),
+        "frac_fp16_peak": round(flops / sec / 1e12 / BF16_PEAK_TFLOPS, 4),
         "reps": reps,
     }
 

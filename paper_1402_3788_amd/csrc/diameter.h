@@ -28,7 +28,8 @@ struct DiameterArgs {
     int64_t n;
     int M;
     float *centroid_ws;       // [M] centre of gravity (written by launch_centroid)
-    uint4 *ah, *al, *bh, *bl; // [npad][4 ks] split operands
+    float *norms;             // [n] squared norms of the centred objects
+    uint4 *ah, *bh;           // [npad][4 ks] fp16 operands
     uint32_t *counters;       // [0] largest |y|^2 (fp32 bits), [1] key of the pass-1 maximum,
                               // [2] nonzero if X holds a NaN or an infinity
     DiamBest *slots;          // [row_blocks * chunks]
@@ -44,7 +45,7 @@ hipError_t launch_centroid(const float *X, int64_t n, int M, double *part, float
                            float *centroid_out, uint32_t *counters, const CentroidPlan &pl,
                            hipStream_t s);
 DiameterPlan plan_diameter(int64_t n, int M);
-// Four launches after launch_centroid: operands, pass 1, pass 2, final.
+// Five launches after launch_centroid: norms, operands, pass 1, pass 2, final.
 hipError_t launch_diameter(const DiameterArgs &a, const DiameterPlan &pl, hipStream_t s);
 
 }  // namespace lloyd

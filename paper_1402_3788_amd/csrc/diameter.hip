@@ -11,21 +11,23 @@
 //
 // Diameter, squared: D2 = max over pairs k < l of |x_k - x_l|^2, with the
 // lexicographically smallest pair reaching it. The all-pairs distances are a
-// Gram matrix (a dense contraction over the features), formed on the bf16
-// matrix cores in split precision, then made exact:
-//   prep    y_i = fl(x_i - C) (centring keeps the norms, and so the error
-//           bound, small against D2), n_i = fl(|y_i|^2); operand rows
-//             a_i = [-2 y_i, 1, n_i, 0 ...],  b_j = [y_j, n_j, 1, 0 ...]
-//           (P = 32 ceil((M+2)/32) features) so that a_i . b_j =
-//           n_i + n_j - 2 y_i.y_j ~ |x_i - x_j|^2 with no epilogue
-//           arithmetic; each operand value v is split into bf16 hi = bf16(v)
-//           and lo = bf16(v - hi), both rounded to nearest, and stored in the
+// Gram matrix (a dense contraction over the features), screened on the fp16
+// matrix cores with one product per 32 features, then made exact:
+//   norms   y_i = fl(x_i - C) (centring keeps the norms, and so the error
+//           bound, small against D2), n_i = fl(|y_i|^2), and the largest n_i;
+//           s = 2^e scales it into [2^12, 2^14): every operand below fits fp16;
+//   prep    operand rows a_i = [-2 s y_i, h_i, 1, l_i, 1, 0 ...],
+//           b_j = [s y_j, 1, h_j, 1, l_j, 0 ...] (P = 32 ceil((M+2)/32)
+//           features) in fp16, rounded to nearest, with h_i = fp16(s^2 n_i) and
+//           l_i = fp16(s^2 n_i - h_i), so that a_i . b_j = s^2 (n_i + n_j - 2
+//           y_i.y_j) ~ s^2 |x_i - x_j|^2 with no epilogue arithmetic; l is left
+//           out where M + 4 features do not fit P; rows are stored in the
 //           matrix instruction's lane order;
-//   pass 1  every pair block is three v_mfma_f32_16x16x32_bf16 per 32
-//           features (lo.hi, hi.lo, hi.hi), exact products summed in fp32;
-//           the maximum approximate value d~* over all pairs is kept (integer
-//           atomic max of an order-preserving key: order-free), and each
-//           work item's own maximum goes to its result slot;
+//   pass 1  every pair block is one v_mfma_f32_16x16x32_f16 per 32 features,
+//           exact products summed in fp32; the maximum approximate value d~*
+//           over all pairs is kept (integer atomic max of an order-preserving
+//           key: order-free), and each work item's own maximum goes to its
+//           result slot;
 //   pass 2  items whose maximum is below the threshold d~* - 2B write an
 //           empty result at once; the others form the same products again,
 //           and every pair k < l with d~ >= d~* - 2B is re-evaluated in fp64
@@ -33,17 +35,25 @@
 //           e = x_j - c_j, d = d + e*e (features ascending, each operation
 //           rounded) and the lexicographic best (largest d, then lowest k,
 //           then lowest l) is kept.
-// B bounds |d~ - d| for every pair: with u = 2^-24, gamma_m = m u / (1 - m u)
+// B bounds |d~ - s^2 d| for every pair: with u = 2^-24, gamma_m = m u / (1 - m u)
 // for this code's own round-to-nearest fp32 arithmetic and
 // phi_m = 2 m u / (1 - 2 m u) for the matrix core's additions (assumed only
 // faithful: each within 2^-23 relative, in any order or direction),
-//   |d~ - d| <= E (|y_k|^2 + |y_l|^2),
-//   E = 4.01 u (centring) + 4.03 * 2^-16 (dropped split terms, three per
-//       feature at most 3.02 * 2^-16 |a b|, and 2^-16 for each norm operand)
-//       + 1.01 gamma_M (the fp32 norms) + 2.02 phi_{3P+2} (the sums),
-// so B = 1.25 * 2.02 * E * max_i n_i covers every pair (1.25: margin). The
-// true pair has d~ >= D2 - B >= d~* - 2B, so it is always re-evaluated, and
-// the result is exact whatever the split products round to.
+//   |d~ - s^2 d| <= E s^2 (|y_k|^2 + |y_l|^2) + A,
+//   E = 4.01 u (centring) + 2.01 * 2^-11 (fp16 y: each factor within 2^-11, and
+//       2 |y_k . y_l| <= |y_k|^2 + |y_l|^2) + 1.01 * 2^-22 (fp16 h + l; 1.01 *
+//       2^-11 without l) + 1.01 gamma_M (the fp32 norms) + 2.02 phi_{P+2} (the
+//       sums),
+//   A = 2^-14 (2 sqrt(M) (|s y_k| + |s y_l|) + M 2^-13 + 4) for operand values
+//       below the normal range of fp16 (2^-14), flushed or not; with
+//       |s y| <= 2^7, A <= 0.27,
+// so B = 1.25 (2.02 E s^2 max_i n_i + A) covers every pair (1.25: margin). The
+// true pair has d~ >= s^2 D2 - B >= d~* - 2B, so it is always re-evaluated, and
+// the result is exact whatever the fp16 products round to. The band 2B is 0.5 %
+// of the largest norm: on random data a handful of pairs lie in it. (The three
+// bf16 split products that this screening took before had a band of 0.06 % and
+// three times the matrix work: pass 1 at n = 500,003, M = 25 took 15.5 ms,
+// now 5.7.)
 //
 // Work: pass items are (row block of 512 objects, column chunk of 16384);
 // items wholly below the diagonal return at once, and within the diagonal
@@ -65,6 +75,12 @@ namespace lloyd {
 namespace {
 
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+
+__device__ inline h8v as_h8(const uint4 &u)
+{
+    return __builtin_bit_cast(h8v, u);
+}
 
 constexpr int kDiamWaves = 8;
 constexpr int kDiamThreads = kDiamWaves * kWave;
@@ -96,8 +112,16 @@ centroid_partial_kernel(const float *__restrict__ X, int64_t total, int M,
     const int T = blockDim.x;                         // a multiple of M
     const int64_t S = (int64_t)gridDim.x * T;
     double s = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * T + threadIdx.x; e < total; e += S)
-        s = s + (double)X[e];
+    // eight loads in flight; past the end the last element's value is not added
+    constexpr int kAhead = 8;
+    for (int64_t e = (int64_t)blockIdx.x * T + threadIdx.x; e < total; e += kAhead * S) {
+        float v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = X[e + u * S < total ? e + u * S : total - 1];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (e + u * S < total) s = s + (double)v[u];
+    }
     csum[threadIdx.x] = s;
     __syncthreads();
     if (threadIdx.x < M) {
@@ -108,15 +132,35 @@ centroid_partial_kernel(const float *__restrict__ X, int64_t total, int M,
 }
 
 // Reads the G partial rows; writes the centroid (fp32) and resets the
-// counters of the diameter passes.
-__global__ void centroid_final_kernel(const double *__restrict__ part, int G, int M, int64_t n,
-                                      float *__restrict__ centroid_ws, float *__restrict__ centroid_out,
-                                      uint32_t *__restrict__ counters)
+// counters of the diameter passes. Row lane r of 16 adds rows r, r + 16, ... of
+// its feature (every load before the first addition), then the 16 sums are
+// added in ascending order. (One thread per feature adding the rows one by one
+// took 60 us.)
+constexpr int kFinalLanes = 16;
+
+__global__ void __launch_bounds__(kFinalLanes * kWave)
+centroid_final_kernel(const double *__restrict__ part, int G, int M, int64_t n,
+                      float *__restrict__ centroid_ws, float *__restrict__ centroid_out,
+                      uint32_t *__restrict__ counters)
 {
-    for (int j = threadIdx.x; j < M; j += blockDim.x) {
-        double s = 0.0;
-        for (int g = 0; g < G; ++g) s = s + part[(int64_t)g * M + j];
-        const float c = (float)(s / (double)n);
+    __shared__ double sums[kFinalLanes][kWave];
+    const int r = threadIdx.x / kWave, j = threadIdx.x % kWave;
+    double v[kCentroidGroups / kFinalLanes];
+#pragma unroll
+    for (int u = 0; u < kCentroidGroups / kFinalLanes; ++u) {
+        const int g = r + kFinalLanes * u;
+        v[u] = (g < G && j < M) ? part[(int64_t)g * M + j] : 0.0;
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < kCentroidGroups / kFinalLanes; ++u) s = s + v[u];
+    sums[r][j] = s;
+    __syncthreads();
+    if (r == 0 && j < M) {
+        double t = 0.0;
+#pragma unroll
+        for (int u = 0; u < kFinalLanes; ++u) t = t + sums[u][j];
+        const float c = (float)(t / (double)n);
         if (centroid_ws) centroid_ws[j] = c;
         if (centroid_out) centroid_out[j] = c;
     }
@@ -125,56 +169,35 @@ __global__ void centroid_final_kernel(const double *__restrict__ part, int G, in
 }
 
 // ---------------------------------------------------------------------------
-// Split-precision operands.
+// Norms and fp16 operands.
 
-template <int KS>
-__global__ void __launch_bounds__(256)
-diam_prep_kernel(const float *__restrict__ X, int64_t n, int64_t npad, int M,
-                 const float *__restrict__ C, uint4 *__restrict__ ah, uint4 *__restrict__ al,
-                 uint4 *__restrict__ bh, uint4 *__restrict__ bl, uint32_t *__restrict__ counters)
+constexpr int kNormThreads = 1024;
+
+// n_i = |x_i - C|^2 in fp32, their maximum and the non-finite flag: persistent
+// workgroups, one atomic each.
+__global__ void __launch_bounds__(kNormThreads)
+diam_norm_kernel(const float *__restrict__ X, int64_t n, int M, const float *__restrict__ C,
+                 float *__restrict__ norms, uint32_t *__restrict__ counters)
 {
-    constexpr int P = 32 * KS;
-    __shared__ float smax[256 / kWave];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    float y[P];
-    float nrm = 0.f;
-    const bool real = i < n;
+    __shared__ float smax[kNormThreads / kWave];
+    float m = 0.f;
     bool finite = true;
-#pragma unroll
-    for (int f = 0; f < P; ++f) {
-        const float x = (real && f < M) ? X[i * M + f] : 0.f;
-        finite = finite && fabsf(x) < INFINITY;
-        y[f] = (real && f < M) ? x - C[f] : 0.f;
-        nrm = nrm + y[f] * y[f];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const float *x = X + i * M;
+        float nrm = 0.f;
+#pragma unroll 8
+        for (int f = 0; f < M; ++f) {
+            const float v = x[f], y = v - C[f];
+            finite = finite && fabsf(v) < INFINITY;
+            nrm = nrm + y * y;
+        }
+        norms[i] = nrm;
+        m = fmaxf(m, nrm);
     }
     // a NaN or an infinite coordinate leaves the diameter undefined: the
     // passes return at once and the result is NaN with the pair (-1, -1)
     if (__ballot(!finite) != 0ull && threadIdx.x % kWave == 0) atomicOr(&counters[2], 1u);
-    if (i < npad) {
-#pragma unroll
-        for (int g = 0; g < 4 * KS; ++g) {
-            float av[8], bv[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int f = 8 * g + e;
-                float a = -2.0f * y[f], b = y[f];
-                if (f == M) { a = 1.0f; b = nrm; }
-                if (f == M + 1) { a = nrm; b = 1.0f; }
-                if (!real) { a = 0.f; b = 0.f; }
-                av[e] = a;
-                bv[e] = b;
-            }
-            uint32_t h[4], l[4];
-            split_bf16x8(av, h, l);
-            ah[i * (4 * KS) + g] = make_uint4(h[0], h[1], h[2], h[3]);
-            al[i * (4 * KS) + g] = make_uint4(l[0], l[1], l[2], l[3]);
-            split_bf16x8(bv, h, l);
-            bh[i * (4 * KS) + g] = make_uint4(h[0], h[1], h[2], h[3]);
-            bl[i * (4 * KS) + g] = make_uint4(l[0], l[1], l[2], l[3]);
-        }
-    }
-    // largest norm of the workgroup, then one order-free atomic max
-    float m = nrm;
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     if (threadIdx.x % kWave == 0) smax[threadIdx.x / kWave] = m;
@@ -184,6 +207,59 @@ diam_prep_kernel(const float *__restrict__ X, int64_t n, int64_t npad, int M,
         for (int w = 1; w < (int)(blockDim.x / kWave); ++w) r = fmaxf(r, smax[w]);
         atomicMax(&counters[0], __float_as_uint(r));          // r >= 0: bits order like values
     }
+}
+
+// Exponent e of the operands' scale s = 2^e: s^2 max n in [2^12, 2^14) (0 for
+// an all-zero or an overflowed norm; the latter re-evaluates every pair).
+__device__ inline int diam_scale_exp(const uint32_t *counters)
+{
+    const float maxn = __uint_as_float(counters[0]);
+    if (!(maxn > 0.f) || !(maxn < INFINITY)) return 0;
+    const int E = ilogbf(maxn);
+    const int d = 13 - E;
+    return d >= 0 ? d / 2 : -((1 - d) / 2);       // floor(d / 2)
+}
+
+// One thread per 16-byte group (8 features) of an operand row.
+__global__ void __launch_bounds__(256)
+diam_prep_kernel(const float *__restrict__ X, int64_t n, int64_t groups, int G4, int M,
+                 const float *__restrict__ C, const float *__restrict__ norms,
+                 const uint32_t *__restrict__ counters, uint4 *__restrict__ ah,
+                 uint4 *__restrict__ bh)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= groups) return;
+    const int64_t i = t / G4;
+    const int g = (int)(t % G4);
+    const bool real = i < n;
+    const bool low = M + 4 <= 8 * G4;             // room for the norms' low parts
+    const int e = diam_scale_exp(counters);
+    h8v a, b;
+    float nh = 0.f, nl = 0.f;
+    if (real) {
+        const float ns = ldexpf(norms[i], 2 * e);
+        nh = (float)(_Float16)ns;
+        nl = ns - nh;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int f = 8 * g + u;
+        float av = 0.f, bv = 0.f;
+        if (real && f < M) {
+            const float y = ldexpf(X[i * M + f] - C[f], e);
+            av = -2.0f * y;
+            bv = y;
+        } else if (real) {
+            if (f == M) { av = nh; bv = 1.0f; }
+            if (f == M + 1) { av = 1.0f; bv = nh; }
+            if (low && f == M + 2) { av = nl; bv = 1.0f; }
+            if (low && f == M + 3) { av = 1.0f; bv = nl; }
+        }
+        a[u] = (_Float16)av;
+        b[u] = (_Float16)bv;
+    }
+    ah[t] = __builtin_bit_cast(uint4, a);
+    bh[t] = __builtin_bit_cast(uint4, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -196,8 +272,8 @@ __device__ inline bool diam_better(double d, int k, int l, double bd, int bk, in
 
 // Threshold of pass 2: d~* - 2B, rounded down to fp32; minus infinity (every
 // pair re-evaluated in fp64) when the largest norm is so large that an fp32
-// pair value may overflow (a value is at most 4 max n_i), where the bound no
-// longer holds.
+// norm may overflow (a pair value is at most 4 max n_i), or so small that the
+// squares in it underflow, where the bound no longer holds.
 template <int KS>
 __device__ inline float diam_threshold(const uint32_t *counters, int M)
 {
@@ -205,10 +281,11 @@ __device__ inline float diam_threshold(const uint32_t *counters, int M)
     const double u = 5.9604644775390625e-8;           // 2^-24
     auto gamma = [&](int m) { return m * u / (1.0 - m * u); };
     auto phi = [&](int m) { return 2.0 * m * u / (1.0 - 2.0 * m * u); };
-    const double E = 4.01 * u + 4.03 * 1.52587890625e-05 + 1.01 * gamma(M) + 2.02 * phi(3 * P + 2);
+    const double norm_err = M + 4 <= P ? 1.01 / 4194304.0 : 1.01 / 2048.0;
+    const double E = 4.01 * u + 2.01 / 2048.0 + norm_err + 1.01 * gamma(M) + 2.02 * phi(P + 2);
     const double maxn = (double)__uint_as_float(counters[0]);
-    if (!(4.0 * maxn < (double)FLT_MAX)) return -INFINITY;
-    const double B = 1.25 * 2.02 * E * maxn;
+    if (!(4.0 * maxn < (double)FLT_MAX) || maxn < 1e-30) return -INFINITY;
+    const double B = 1.25 * (2.02 * E * ldexp(maxn, 2 * diam_scale_exp(counters)) + 0.27);
     const double thr = (double)key_float(counters[1]) - 2.0 * B;
     float t = (float)thr;
     if ((double)t > thr) t = nextafterf(t, -INFINITY);
@@ -233,19 +310,17 @@ __device__ __attribute__((noinline)) double diam_exact_d2(const float *__restric
 
 template <int KS, bool kExact>
 __device__ __forceinline__ void
-diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
-               const uint4 *__restrict__ bh, const uint4 *__restrict__ bl, int64_t n,
+diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64_t n,
                int64_t nsteps_total, const float *__restrict__ X, int M,
                uint32_t *__restrict__ counters, DiamBest *__restrict__ slots)
 {
     constexpr int G4 = 4 * KS;                        // 16-byte groups per operand row
     constexpr int kLdsRow = G4 + 1;                   // uint4 per LDS row (16 bytes padding)
     constexpr int kQuads = 64 * G4;                   // 16-byte groups per step and array
-    constexpr int kPer = 2 * kQuads / kDiamThreads;   // groups each thread copies (= KS)
-    static_assert(2 * kQuads == kPer * kDiamThreads, "copy split");
-    // two buffers (the step computed and the step being staged), hi and lo
-    __shared__ uint4 sb[2][2][64 * kLdsRow];
-    __shared__ float wmax[kDiamWaves];
+    constexpr int kPer = (kQuads + kDiamThreads - 1) / kDiamThreads;   // groups a thread copies
+    // two buffers: the step computed and the step being staged
+    __shared__ uint4 sb[2][64 * kLdsRow];
+    __shared__ int wmax[kDiamWaves];
     __shared__ DiamBest wbest[kDiamWaves];
 
     if (counters[2] != 0u) return;                    // non-finite input (uniform)
@@ -264,9 +339,10 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
     float thr = 0.f;
     if constexpr (kExact) {
         // pass 1 left this item's largest value in its slot: an item with no
-        // value at the threshold has no candidate pair
+        // value at the threshold has no candidate pair (a NaN, possible only
+        // when thr is minus infinity, is kept)
         thr = diam_threshold<KS>(counters, M);
-        if (!(slots[slot].d >= (double)thr)) {
+        if (slots[slot].d < (double)thr) {
             __syncthreads();                          // every thread has read the slot
             if (threadIdx.x == 0) slots[slot] = DiamBest{-1.0, INT_MAX, INT_MAX};
             return;
@@ -274,39 +350,33 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
     }
 
     // A operands of this wave's 64 rows: 4 row blocks x KS steps of 32 features
-    uint32_t a_hi[4][KS][4], a_lo[4][KS][4];
+    uint4 a_op[4][KS];
     const int64_t r0 = I0 + 64 * w;
 #pragma unroll
     for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int64_t row = r0 + 16 * rb + lane % 16;
-            const uint4 h = ah[row * G4 + ks * 4 + lane / 16];
-            const uint4 l = al[row * G4 + ks * 4 + lane / 16];
-            a_hi[rb][ks][0] = h.x; a_hi[rb][ks][1] = h.y; a_hi[rb][ks][2] = h.z; a_hi[rb][ks][3] = h.w;
-            a_lo[rb][ks][0] = l.x; a_lo[rb][ks][1] = l.y; a_lo[rb][ks][2] = l.z; a_lo[rb][ks][3] = l.w;
-        }
+        for (int ks = 0; ks < KS; ++ks)
+            a_op[rb][ks] = ah[(r0 + 16 * rb + lane % 16) * G4 + ks * 4 + lane / 16];
 
-    // staging: thread t copies groups q = t + 512 u of the hi array, then the lo array
+    // staging: thread t copies groups t, t + 512, ... (past the last: the last)
     uint4 pf[kPer];
+    auto group_of = [&](int u) {
+        const int q = threadIdx.x + kDiamThreads * u;
+        return q < kQuads ? q : kQuads - 1;
+    };
     auto fetch = [&](int64_t s) {
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int q = threadIdx.x + kDiamThreads * u;
-            const int qq = q < kQuads ? q : q - kQuads;
-            pf[u] = (q < kQuads ? bh : bl)[(s * 64 + qq / G4) * G4 + qq % G4];
-        }
+        for (int u = 0; u < kPer; ++u) pf[u] = bh[s * kQuads + group_of(u)];
     };
     auto stage = [&](int buf) {
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
-            const int q = threadIdx.x + kDiamThreads * u;
-            const int qq = q < kQuads ? q : q - kQuads;
-            sb[buf][q < kQuads ? 0 : 1][(qq / G4) * kLdsRow + qq % G4] = pf[u];
+            const int q = group_of(u);
+            sb[buf][(q / G4) * kLdsRow + q % G4] = pf[u];
         }
     };
 
-    float vmax = -INFINITY;
+    int vmax = 0;
     double bd = -1.0;
     int bk = INT_MAX, bl_ = INT_MAX;
 
@@ -317,11 +387,9 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
         const int buf = (int)((s - s_lo) & 1);
         const bool more = s + 1 < s_hi;
         if (more) fetch(s + 1);                       // in flight during this step
-        const uint4 *lh = sb[buf][0], *ll = sb[buf][1];
+        const uint4 *lh = sb[buf];
 
-        // the step's 64 columns in two halves of 32 (2 column blocks): with 32
-        // accumulator registers per half, 32 features fit 4 waves per SIMD
-        // (two workgroups per compute unit)
+        // the step's 64 columns in two halves of 32 (2 column blocks)
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             f4v acc[4][2];
@@ -331,54 +399,37 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
                 for (int cc = 0; cc < 2; ++cc) acc[rb][cc] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                // one operand set at a time: the hi parts of B with both parts
-                // of A, then the lo parts of B with hi(A)
-                uint32_t b[2][4];
+                uint4 b[2];
 #pragma unroll
-                for (int cc = 0; cc < 2; ++cc) {
-                    const int o = 16 * (2 * half + cc) + lane % 16;
-                    const uint4 h = lh[o * kLdsRow + ks * 4 + lane / 16];
-                    b[cc][0] = h.x; b[cc][1] = h.y; b[cc][2] = h.z; b[cc][3] = h.w;
-                }
+                for (int cc = 0; cc < 2; ++cc)
+                    b[cc] = lh[(16 * (2 * half + cc) + lane % 16) * kLdsRow + ks * 4 + lane / 16];
 #pragma unroll
                 for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
                     for (int cc = 0; cc < 2; ++cc)
-                        acc[rb][cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf8(a_lo[rb][ks]), as_bf8(b[cc]), acc[rb][cc], 0, 0, 0);
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-                    for (int cc = 0; cc < 2; ++cc)
-                        acc[rb][cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf8(a_hi[rb][ks]), as_bf8(b[cc]), acc[rb][cc], 0, 0, 0);
-#pragma unroll
-                for (int cc = 0; cc < 2; ++cc) {
-                    const int o = 16 * (2 * half + cc) + lane % 16;
-                    const uint4 l = ll[o * kLdsRow + ks * 4 + lane / 16];
-                    b[cc][0] = l.x; b[cc][1] = l.y; b[cc][2] = l.z; b[cc][3] = l.w;
-                }
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-                    for (int cc = 0; cc < 2; ++cc)
-                        acc[rb][cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf8(a_hi[rb][ks]), as_bf8(b[cc]), acc[rb][cc], 0, 0, 0);
+                        acc[rb][cc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            as_h8(a_op[rb][ks]), as_h8(b[cc]), acc[rb][cc], 0, 0, 0);
             }
 
-            // the largest value of the half in this lane (padding rows and
-            // columns give exactly 0, never above a real pair's value by more
-            // than the bound; pairs i >= j repeat pairs i < j)
-            float smax = -INFINITY;
+            // the largest value of the half in this lane, or 0: the order of
+            // the bits of non-negative floats as integers (a positive NaN
+            // above all), negative values (error around 0) below 0. One
+            // three-way maximum per two values; the floating-point form made
+            // the compiler quiet every operand first (9.5 ms against 5.7 in
+            // pass 1). Padding rows and columns give exactly 0, and pairs i >=
+            // j repeat pairs i < j.
+            int smax = 0;
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-                for (int cc = 0; cc < 2; ++cc)
-                    smax = fmaxf(fmaxf(smax, fmaxf(acc[rb][cc][0], acc[rb][cc][1])),
-                                 fmaxf(acc[rb][cc][2], acc[rb][cc][3]));
+                for (int cc = 0; cc < 2; ++cc) {
+                    auto bits = [&](int r) { return __float_as_int(acc[rb][cc][r]); };
+                    smax = max(max(smax, bits(0)), bits(1));
+                    smax = max(max(smax, bits(2)), bits(3));
+                }
             if constexpr (!kExact) {
-                vmax = fmaxf(vmax, smax);
-            } else if (__builtin_amdgcn_ballot_w64(!(smax < thr)) != 0) {
+                vmax = max(vmax, smax);
+            } else if (__builtin_amdgcn_ballot_w64(!(__int_as_float(smax) < thr)) != 0) {
                 // rare: some pair of this wave's half step reaches the threshold
                 const int64_t c0 = s * 64 + 32 * half;
 #pragma unroll
@@ -409,14 +460,15 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
 
     if constexpr (!kExact) {
 #pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, off));
+        for (int off = kWave / 2; off > 0; off >>= 1) vmax = max(vmax, __shfl_xor(vmax, off));
         if (lane == 0) wmax[w] = vmax;
         __syncthreads();
         if (threadIdx.x == 0) {
-            float m = wmax[0];
-            for (int k = 1; k < kDiamWaves; ++k) m = fmaxf(m, wmax[k]);
-            atomicMax(&counters[1], float_key(m));
-            slots[slot] = DiamBest{(double)m, INT_MAX, INT_MAX};   // read by pass 2
+            int m = wmax[0];
+            for (int k = 1; k < kDiamWaves; ++k) m = max(m, wmax[k]);
+            const float v = __int_as_float(m);
+            atomicMax(&counters[1], float_key(v));
+            slots[slot] = DiamBest{(double)v, INT_MAX, INT_MAX};   // read by pass 2
         }
     } else {
 #pragma unroll
@@ -442,12 +494,11 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
 
 template <int KS, bool kExact>
 __global__ void __launch_bounds__(kDiamThreads)
-diam_pass_kernel(const uint4 *__restrict__ ah, const uint4 *__restrict__ al,
-                 const uint4 *__restrict__ bh, const uint4 *__restrict__ bl, int64_t n,
+diam_pass_kernel(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64_t n,
                  int64_t nsteps_total, const float *__restrict__ X, int M,
                  uint32_t *__restrict__ counters, DiamBest *__restrict__ slots)
 {
-    diam_pass_body<KS, kExact>(ah, al, bh, bl, n, nsteps_total, X, M, counters, slots);
+    diam_pass_body<KS, kExact>(ah, bh, n, nsteps_total, X, M, counters, slots);
 }
 
 // The lexicographic best of all item slots. With n = 1 there is no pair:
@@ -503,19 +554,25 @@ diam_final_kernel(const DiamBest *__restrict__ slots, int64_t nslots, int64_t n,
 template <int KS>
 hipError_t diam_launch_ks(const DiameterArgs &a, const DiameterPlan &pl, hipStream_t s)
 {
-    const dim3 gprep((unsigned)((pl.npad + 255) / 256));
-    hipLaunchKernelGGL(diam_prep_kernel<KS>, gprep, dim3(256), 0, s, a.X, a.n, pl.npad, a.M,
-                       a.centroid_ws, a.ah, a.al, a.bh, a.bl, a.counters);
+    const int64_t want = (a.n + kNormThreads - 1) / kNormThreads;
+    const dim3 gnorm((unsigned)(want < kCUs ? want : kCUs));
+    hipLaunchKernelGGL(diam_norm_kernel, gnorm, dim3(kNormThreads), 0, s, a.X, a.n, a.M,
+                       a.centroid_ws, a.norms, a.counters);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const int64_t groups = pl.npad * 4 * KS;
+    hipLaunchKernelGGL(diam_prep_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s,
+                       a.X, a.n, groups, 4 * KS, a.M, a.centroid_ws, a.norms, a.counters, a.ah,
+                       a.bh);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 grid((unsigned)pl.row_blocks, (unsigned)pl.chunks);
     const int64_t nsteps = pl.npad / 64;
     auto pass1 = diam_pass_kernel<KS, false>;
     auto pass2 = diam_pass_kernel<KS, true>;
-    hipLaunchKernelGGL(pass1, grid, dim3(kDiamThreads), 0, s, a.ah, a.al, a.bh, a.bl, a.n,
+    hipLaunchKernelGGL(pass1, grid, dim3(kDiamThreads), 0, s, a.ah, a.bh, a.n,
                        nsteps, a.X, a.M, a.counters, a.slots);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(pass2, grid, dim3(kDiamThreads), 0, s, a.ah, a.al, a.bh, a.bl, a.n,
+    hipLaunchKernelGGL(pass2, grid, dim3(kDiamThreads), 0, s, a.ah, a.bh, a.n,
                        nsteps, a.X, a.M, a.counters, a.slots);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(diam_final_kernel, dim3(1), dim3(1024), 0, s, a.slots,
@@ -543,7 +600,7 @@ hipError_t launch_centroid(const float *X, int64_t n, int M, double *part, float
                        (size_t)pl.threads * sizeof(double), s, X, n * M, M, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(centroid_final_kernel, dim3(1), dim3(64), 0, s, part, pl.groups, M, n,
+    hipLaunchKernelGGL(centroid_final_kernel, dim3(1), dim3(kFinalLanes * kWave), 0, s, part, pl.groups, M, n,
                        centroid_ws, centroid_out, counters);
     return hipGetLastError();
 }
