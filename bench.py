@@ -205,8 +205,8 @@ BF16_PEAK_TFLOPS = 2500.0       # MI355X dense bf16 (and fp16) matrix peak
 
 
 def time_diameter(torch, km, Xg, reps=2):
-    """Priced as one screening pass over the n(n-1)/2 pairs: one fp16 matrix
-    products over 32 ceil((M+2)/32) features per pair (the second pass only
+    """Priced as one screening pass over the n(n-1)/2 pairs: one fp16 matrix product
+    over 32 ceil((M+2)/32) features per pair (the second pass only
     revisits the few work items whose maximum reaches the threshold)."""
     n, M = Xg.shape
     ws = torch.empty(km.kmeans_diameter_workspace_bytes(n, M), dtype=torch.uint8,

@@ -309,6 +309,20 @@ int run_impl(const float *X, int64_t n, int32_t M, int32_t K, const float *init_
         return hip_status(hipEventRecord(cache.ev[nev++], s));
     };
 
+    // The control block after iteration `done`, in *host: through a launch that
+    // stores it to the pinned copy, else through the runtime's copy.
+    bool current = false;
+    auto read_back = [&](int done) -> int {
+        int r;
+        if (host == &pageable)
+            r = hip_status(hipMemcpyAsync(host, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
+        else
+            r = hip_status(launch_ctl_report(ctl, host, done, fixed, s));
+        if (!r) r = hip_status(hipStreamSynchronize(s));
+        current = r == KMEANS_OK;
+        return r;
+    };
+
     // Two launches per iteration: assign + accumulate (fused), then the centres
     // and the congruence test from the workgroup partials. Iteration t assigns
     // with the centres of iteration t - 1: the caller's initial centres for
@@ -355,14 +369,13 @@ int run_impl(const float *X, int64_t n, int32_t M, int32_t K, const float *init_
         }
         t = end + 1;
         if (rc || t > max_iter) break;
-        rc = hip_status(hipMemcpyAsync(host, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-        if (!rc) rc = hip_status(hipStreamSynchronize(s));
+        rc = read_back(end);
         if (rc || host->converged_at != 0) break;
         chunk = chunk * 2 < 64 ? chunk * 2 : 64;
     }
     if (!rc) rc = mark();
-    if (!rc) rc = hip_status(hipMemcpyAsync(host, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-    if (!rc) rc = hip_status(hipStreamSynchronize(s));
+    // (a run that has just been found converged is already read)
+    if (!rc && !(current && !timing && host->converged_at != 0)) rc = read_back(launched);
     if (rc) return rc;
     *iterations = host->converged_at != 0 ? host->converged_at : max_iter;
     if (host->ring_stalls != 0) rc = KMEANS_EHIP;

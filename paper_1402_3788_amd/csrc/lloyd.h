@@ -87,6 +87,18 @@ inline size_t static_lds_bytes(const void *kernel)
     return attr.sharedSizeBytes;
 }
 
+// Launch of an assigning kernel: through hipExtLaunchKernel with the step's
+// events when it is timed, else the plain way, which takes the host less time
+// (a run of few objects is bound by its launches).
+#define LLOYD_STEP_LAUNCH(kern, grid, block, lds, s, a, ...)                                      \
+    do {                                                                                          \
+        if ((a).ev_start != nullptr)                                                              \
+            hipExtLaunchKernelGGL(kern, grid, block, lds, s, (a).ev_start, (a).ev_stop, 0,        \
+                                  __VA_ARGS__);                                                   \
+        else                                                                                      \
+            hipLaunchKernelGGL(kern, grid, block, lds, s, __VA_ARGS__);                           \
+    } while (0)
+
 struct AccumPlan {
     Path path;
     int waves;          // wavefronts per workgroup
@@ -140,6 +152,8 @@ hipError_t launch_tile(const StepArgs &a, Mode mode, const AccumPlan &plan, hipS
 hipError_t launch_accum(const StepArgs &a, const AccumPlan &plan, hipStream_t s);
 
 hipError_t launch_ctl_reset(Ctl *ctl, hipStream_t s);
+// The block after iteration t, written to pinned host memory.
+hipError_t launch_ctl_report(Ctl *ctl, Ctl *host, int t, int fixed, hipStream_t s);
 
 // Centres of gravity and change flag of iteration a.t from the partials of an
 // accumulating launch with `groups` workgroups (lloyd_centres.hip).

@@ -438,8 +438,22 @@ __device__ inline void write_wave_partials(const double *slabs, int W, int K, in
     const size_t rows = (size_t)W * P;          // slabs in the workgroup
     for (int e = tid; e < K * MW; e += nthr) {
         const int k = e / MW, j = e - (e / MW) * MW;
+        // eight reads in flight ahead of their additions (a wave of a small
+        // shape owns up to 32 slabs: read one by one, 192 of them took 4 of
+        // the launch's 6.4 us at M = 2)
+        constexpr int kAhead = 8;
+        const double *col = slabs + (size_t)k * MW + j;
+        const size_t step = (size_t)rows_per_slab * MW;
         double s = 0.0;
-        for (size_t r = 0; r < rows; ++r) s = s + slabs[(r * rows_per_slab + k) * MW + j];
+        size_t r = 0;
+        for (; r + kAhead <= rows; r += kAhead) {
+            double v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = col[(r + u) * step];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) s = s + v[u];
+        }
+        for (; r < rows; ++r) s = s + col[r * step];
         if (j < M) part_sums[(int64_t)k * M + j] = s;
         else counts_col[(int64_t)k * cstride] = (int32_t)s;
     }

@@ -57,6 +57,9 @@ constexpr int kL1 = 1;
 // two-launch form; K = 64, n = 2e7: 2,110 against 1,954.
 constexpr int kL1FusedMinWaves = 8;
 constexpr int kL1FusedMaxK = 32;
+// Sums of a workgroup up to which few tiles are spread (256 rows of 2048
+// sums: 4 MB of partials).
+[[maybe_unused]] constexpr int kSpreadKM = 2048;
 
 // Per-wave tile slot: the 64 objects plus slack.
 __host__ __device__ inline size_t lane_tile_bytes(int M)
@@ -270,7 +273,7 @@ hipError_t launch_m(const StepArgs &a, Mode mode, const AccumPlan &p, hipStream_
         static const size_t st = static_lds_bytes(reinterpret_cast<const void *>(kern));       \
         if (st > (size_t)kMaxLds || st + p.lds_bytes > (size_t)kMaxLds)                        \
             return hipErrorInvalidConfiguration;                                               \
-        hipExtLaunchKernelGGL(kern, grid, block, p.lds_bytes, s, a.ev_start, a.ev_stop, 0,     \
+        LLOYD_STEP_LAUNCH(kern, grid, block, p.lds_bytes, s, a,                                \
                               a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,            \
                               a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64);    \
     } while (0)
@@ -303,8 +306,7 @@ hipError_t launch_l1_m(const StepArgs &a, const AccumPlan &p, hipStream_t s)
     const size_t st = p.accum == 1 ? st1 : st0;
     if (st > (size_t)kMaxLds || st + p.lds_bytes > (size_t)kMaxLds)
         return hipErrorInvalidConfiguration;
-    hipExtLaunchKernelGGL(kern, dim3(p.groups), dim3(p.waves * kWave), p.lds_bytes, s, a.ev_start,
-                          a.ev_stop, 0, a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,
+    LLOYD_STEP_LAUNCH(kern, dim3(p.groups), dim3(p.waves * kWave), p.lds_bytes, s, a, a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,
                           a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64);
     return hipGetLastError();
 }
@@ -387,6 +389,9 @@ AccumPlan plan_lane(int64_t n, int M, int K, Mode mode)
     }
     const int64_t nq = (n + kWave - 1) / kWave;
     while (W > 1 && W / 2 >= nq) W /= 2;
+    // few tiles: spread them over the compute units in small workgroups, where
+    // the additional rows of partials are short
+    while (W > 1 && K * M <= kSpreadKM && (nq + W - 1) / W < kCUs) W /= 2;
     int64_t groups = (nq + W - 1) / W;
     if (groups > kCUs) groups = kCUs;       // one persistent workgroup per compute unit
     p.waves = W;

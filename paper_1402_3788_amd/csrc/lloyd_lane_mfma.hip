@@ -779,7 +779,7 @@ hipError_t launch_mb(const StepArgs &a, Mode mode, const AccumPlan &p, hipStream
         static const size_t st = static_lds_bytes(reinterpret_cast<const void *>(kern));       \
         if (st > (size_t)kMaxLds || st + p.lds_bytes > (size_t)kMaxLds)                        \
             return hipErrorInvalidConfiguration;                                               \
-        hipExtLaunchKernelGGL(kern, grid, block, p.lds_bytes, s, a.ev_start, a.ev_stop, 0,     \
+        LLOYD_STEP_LAUNCH(kern, grid, block, p.lds_bytes, s, a,                                \
                               a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,            \
                               a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64);    \
     } while (0)
