@@ -198,23 +198,15 @@ lloyd_lane_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                     if constexpr (METRIC == kL1) d = d + fabsf(e);
                     else d = __builtin_fmaf(e, e, d);
                 }
-                if constexpr (METRIC == kL1) {
-                    // a NaN distance changes neither
-                    if (d < b1) {
-                        b2 = b1;
-                        b1 = d;
-                        lab = k;
-                    } else if (d < b2) {
-                        b2 = d;
-                    }
-                } else {
-                    // top-2: with b1 <= b2, the new second-best is the median
-                    // of (b1, b2, d) and the new best is min(b1, d)
-                    const bool lt = d < b1;
-                    b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
-                    b1 = lt ? d : b1;
-                    lab = lt ? k : lab;
-                }
+                // top-2: with b1 <= b2, the new second-best is the median
+                // of (b1, b2, d) and the new best is min(b1, d). A NaN
+                // distance never becomes the best; as the median of it the
+                // second best may come down to b1, which only sends the
+                // object to the fp64 decision.
+                const bool lt = d < b1;
+                b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
+                b1 = lt ? d : b1;
+                lab = lt ? k : lab;
             }
             bool ok;
             if constexpr (METRIC == kL1)
