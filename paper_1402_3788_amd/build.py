@@ -77,7 +77,7 @@ def build(verbose: bool = True, jobs: int = 8, incremental: bool = False) -> str
             ot = os.path.getmtime(obj)
             if ot > os.path.getmtime(os.path.join(CSRC, src)) and ot > head_t:
                 continue
-        cmd = [hipcc(), *HIPCC_FLAGS, *extra, *os.environ.get("KMEANS_HIPCC_EXTRA", "").split(), "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc(), *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
         while sum(p.poll() is None for _, p in procs) >= jobs:
             time.sleep(0.05)

@@ -153,8 +153,8 @@ hipError_t l1_launch_m(const StepArgs &a, const L1Plan &pl, hipStream_t s)
     static const size_t st = static_lds_bytes(reinterpret_cast<const void *>(kern));
     if (st > (size_t)kMaxLds || st + pl.lds_bytes > (size_t)kMaxLds)
         return hipErrorInvalidConfiguration;
-    LLOYD_STEP_LAUNCH(kern, dim3(pl.groups), dim3(pl.waves * kWave), pl.lds_bytes, s, a, a.X, a.n, a.C, a.K, a.labels, a.min_d2, a.ctl,
-                          a.t, a.fixed, a.force64);
+    LLOYD_STEP_LAUNCH(kern, dim3(pl.groups), dim3(pl.waves * kWave), pl.lds_bytes, s, a, a.X, a.n,
+                      a.C, a.K, a.labels, a.min_d2, a.ctl, a.t, a.fixed, a.force64);
     return hipGetLastError();
 }
 

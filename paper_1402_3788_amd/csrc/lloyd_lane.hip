@@ -298,7 +298,8 @@ hipError_t launch_l1_m(const StepArgs &a, const AccumPlan &p, hipStream_t s)
     const size_t st = p.accum == 1 ? st1 : st0;
     if (st > (size_t)kMaxLds || st + p.lds_bytes > (size_t)kMaxLds)
         return hipErrorInvalidConfiguration;
-    LLOYD_STEP_LAUNCH(kern, dim3(p.groups), dim3(p.waves * kWave), p.lds_bytes, s, a, a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,
+    LLOYD_STEP_LAUNCH(kern, dim3(p.groups), dim3(p.waves * kWave), p.lds_bytes, s, a, a.X, a.n,
+                      a.C, a.K, a.labels, a.labels_in, a.min_d2,
                           a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64);
     return hipGetLastError();
 }
@@ -311,30 +312,16 @@ using LaunchL1Fn = hipError_t (*)(const StepArgs &, const AccumPlan &, hipStream
 constexpr int kPartLo = LLOYD_PART * kMaxM / LLOYD_PARTS + 1;
 constexpr int kPartN = kMaxM / LLOYD_PARTS;
 
-template <int M>
-constexpr LaunchFn entry()
-{
-    if constexpr (!lloyd_built(M)) return nullptr;
-    else return &launch_m<M>;
-}
-
 template <int... Is>
 constexpr auto make_table(std::integer_sequence<int, Is...>)
 {
-    return std::array<LaunchFn, sizeof...(Is)>{entry<kPartLo + Is>()...};
-}
-
-template <int M>
-constexpr LaunchL1Fn entry_l1()
-{
-    if constexpr (!lloyd_built(M)) return nullptr;
-    else return &launch_l1_m<M>;
+    return std::array<LaunchFn, sizeof...(Is)>{&launch_m<kPartLo + Is>...};
 }
 
 template <int... Is>
 constexpr auto make_l1_table(std::integer_sequence<int, Is...>)
 {
-    return std::array<LaunchL1Fn, sizeof...(Is)>{entry_l1<kPartLo + Is>()...};
+    return std::array<LaunchL1Fn, sizeof...(Is)>{&launch_l1_m<kPartLo + Is>...};
 }
 
 }  // namespace

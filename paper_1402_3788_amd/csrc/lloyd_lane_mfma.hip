@@ -812,7 +812,7 @@ constexpr int kPartN = kMaxM / LLOYD_PARTS;
 template <int M>
 constexpr LaunchFn entry()
 {
-    if constexpr (M <= kMaxMLane && lloyd_built(M)) return &launch_m<M>;
+    if constexpr (M <= kMaxMLane) return &launch_m<M>;
     else return nullptr;
 }
 

@@ -14,19 +14,6 @@
 #define LLOYD_PART_FN(name) LLOYD_CAT(name, LLOYD_PART)
 #define LLOYD_PART_CASES LLOYD_CASE(0) LLOYD_CASE(1) LLOYD_CASE(2) LLOYD_CASE(3)
 
-// The feature counts that are built: all of them, unless the build names a few
-// (LLOYD_ONLY_MS, a comma-separated list, for short development builds).
-constexpr bool lloyd_built([[maybe_unused]] int M)
-{
-#ifdef LLOYD_ONLY_MS
-    for (int m : {LLOYD_ONLY_MS})
-        if (m == M) return true;
-    return false;
-#else
-    return true;
-#endif
-}
-
 static_assert(lloyd::kMaxM % LLOYD_PARTS == 0, "parts split the feature counts evenly");
 
 namespace lloyd {

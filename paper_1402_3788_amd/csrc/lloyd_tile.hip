@@ -1008,17 +1008,10 @@ using LaunchFn = hipError_t (*)(const StepArgs &, Mode, const AccumPlan &, hipSt
 constexpr int kPartLo = LLOYD_PART * kMaxM / LLOYD_PARTS + 1;
 constexpr int kPartN = kMaxM / LLOYD_PARTS;
 
-template <int M>
-constexpr LaunchFn entry()
-{
-    if constexpr (!lloyd_built(M)) return nullptr;
-    else return &launch_m<M>;
-}
-
 template <int... Is>
 constexpr auto make_table(std::integer_sequence<int, Is...>)
 {
-    return std::array<LaunchFn, sizeof...(Is)>{entry<kPartLo + Is>()...};
+    return std::array<LaunchFn, sizeof...(Is)>{&launch_m<kPartLo + Is>...};
 }
 
 }  // namespace
