@@ -343,9 +343,9 @@ def main():
                      "assign_launches_timed": nsamp},
         "kernel_avg_us": round(assign_us, 3),
         "iteration_avg_us": round(iteration_us, 3),
-        # close calls of the timed run, per iteration: 64-object tiles whose
-        # split-precision scores were recomputed with fp32 products (tile
-        # kernel), objects re-decided in fp64 (both kernels)
+        # close calls of the timed run, per iteration: columns of up to 16
+        # objects scored again (tile kernel), objects decided again (both
+        # kernels)
         "reruns_per_iteration": round(reruns / args.steps, 2),
         "fallbacks_per_iteration": round(fallbacks / args.steps, 2),
         "roofline": {
@@ -362,10 +362,12 @@ def main():
     }
 
     if key == "tiles":
-        # the 64-object-tile kernel is matrix-bound for large K: its first pass
-        # issues three bf16 products per 16 x 16 block of (object, centre) pairs
-        # over 32 ceil(M/32) features (tiles with a close call add fp32 products)
-        flops = 3 * 2 * (64 * -(-n // 64)) * (16 * -(-K // 16)) * (32 * -(-M // 32))
+        # the 64-object-tile kernel is matrix-bound for large K: it issues three
+        # bf16 products per 16 x 16 block of (object, centre) pairs and 32
+        # features, two (one) for a last chunk of at most 16 (8) features
+        last = M - 32 * (-(-M // 32) - 1)
+        products = 3 * (-(-M // 32) - 1) + (1 if last <= 8 else 2 if last <= 16 else 3)
+        flops = products * 2 * (64 * -(-n // 64)) * (16 * -(-K // 16)) * 32
         tf = flops / (assign_us * 1e-6) / 1e12
         result["roofline_mfma"] = {"bound": "mfma", "achieved": round(tf, 1),
                                    "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s",

@@ -336,13 +336,14 @@ def kmeans_run_noalloc(X: torch.Tensor, K: int, init_centers: torch.Tensor, max_
 
 
 def ctl_fallbacks(ws: torch.Tensor) -> int:
-    """Objects re-decided in fp64 during the last kmeans_run that used `ws`
-    (read from the control block at the start of the workspace)."""
+    """Objects whose label the scores left open, decided again during the last
+    kmeans_run that used `ws` (read from the control block at the start of the
+    workspace)."""
     return int(ws[12:16].view(torch.int32).item())
 
 
 def ctl_reruns(ws: torch.Tensor) -> int:
-    """64-object tiles of the tile kernel whose split-precision scores left a
-    call too close, recomputed with fp32 products, during the last kmeans_run
-    that used `ws` (read from the control block)."""
+    """Columns of up to 16 close calls that the tile kernel gathered and scored
+    again, and batches of up to 64 that it decided without, during the last
+    kmeans_run that used `ws` (read from the control block)."""
     return int(ws[16:20].view(torch.int32).item())
