@@ -121,6 +121,8 @@ bool tile_fits(int M, int K);
 // Whether the one-object-per-lane matrix-core form supports this shape (its
 // centre operands live in registers: K <= 16, M <= 32).
 bool lane_mfma_fits(int M, int K);
+// Where that form's table of slab offsets starts in LDS (bytes).
+size_t lane_mfma_offs_at(int M, int K, int W);
 
 struct StepArgs {
     const float *X;

@@ -128,16 +128,22 @@ __host__ __device__ constexpr bool lane_a_in_lds(int KB) { return KB > 1; }
 
 // LDS of a workgroup: with accumulation [W][S][K + 1][M] fp64 slabs and
 // [W][K + 1] int32 counts (the last row and count take the adds of close
-// calls) and [W][64] int32 slab offsets of the objects of the current tile
-// (rounded up to 16 bytes); with distances, the A table [3][KB][64] x 16 bytes
+// calls) and [W][64] int32 slab offsets of the objects of the current tile;
+// with distances, the A table [3][KB][64] x 16 bytes
 // when there is more than one block; in assignments the centres [K][M] in fp32
 // (for the distances that may be asked for); then a list of close calls per
 // wave (object indices) in what is left of the launch's share.
-[[maybe_unused]] __host__ __device__ inline size_t lane_acc_bytes(int M, int K, int W)
+// Offset of the slab offsets: a multiple of 16, which the counts before them
+// (W (K + 1) of four bytes) are not for one or two waves, because the offsets
+// are read 16 bytes at a time.
+[[maybe_unused]] __host__ __device__ inline size_t lane_offs_at(int M, int K, int W)
 {
     const int S = lane_slabs(lane_blocks(K));
-    return ((size_t)W * S * (K + 1) * M * 8 + (size_t)W * (K + 1) * 4 + (size_t)W * kWave * 4 + 15) &
-           ~size_t(15);
+    return ((size_t)W * S * (K + 1) * M * 8 + (size_t)W * (K + 1) * 4 + 15) & ~size_t(15);
+}
+[[maybe_unused]] __host__ __device__ inline size_t lane_acc_bytes(int M, int K, int W)
+{
+    return lane_offs_at(M, K, W) + (size_t)W * kWave * 4;
 }
 [[maybe_unused]] __host__ __device__ inline size_t lane_tab_bytes(int K, Mode mode)
 {
@@ -291,8 +297,7 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     double *slabs = reinterpret_cast<double *>(smem) + (size_t)wave * S * KR * M;
     int32_t *cnts = reinterpret_cast<int32_t *>(reinterpret_cast<double *>(smem) +
                                                 (size_t)W * S * KR * M) + wave * KR;
-    int32_t *offs = reinterpret_cast<int32_t *>(reinterpret_cast<double *>(smem) +
-                                                (size_t)W * S * KR * M) + W * KR + wave * kWave;
+    int32_t *offs = reinterpret_cast<int32_t *>(smem + lane_offs_at(M, K, W)) + wave * kWave;
     if (kAcc) {
         for (int i = lane; i < S * KR * M; i += kWave) slabs[i] = 0.0;
         for (int i = lane; i < KR; i += kWave) cnts[i] = 0;
@@ -834,6 +839,8 @@ hipError_t LLOYD_PART_FN(launch_lane_mfma_part)(const StepArgs &a, Mode mode, co
 }
 
 #if LLOYD_PART == 0
+size_t lane_mfma_offs_at(int M, int K, int W) { return lane_offs_at(M, K, W); }
+
 bool lane_mfma_fits(int M, int K)
 {
     return K <= kMaxKLane && M <= kMaxMLane;   // (the slabs of K = 64, M = 32 leave 470 list places)
