@@ -104,6 +104,7 @@ struct AccumPlan {
     int waves;          // wavefronts per workgroup
     int groups;         // workgroups (persistent, strided over 64-object tiles)
     int accum;          // accumulation form (kernel-specific code)
+    int list_cap;       // close calls a wave can note (matrix-core kernels)
     size_t lds_bytes;   // dynamic LDS per workgroup
 };
 

@@ -123,9 +123,8 @@ __host__ __device__ inline int a_operands(int M)
 
 // LDS carve-up of a workgroup (dynamic shared memory).
 struct MfmaLds {
-    size_t abf, cnorm, misc, tiles, offs, slab, list, total;
+    size_t abf, cnorm, misc, tiles, offs, slab, list;
     int tile_floats;
-    int list_cap;       // close calls a wave can note
 };
 
 __host__ __device__ inline size_t al16(size_t v) { return (v + 15) & ~size_t(15); }
@@ -174,11 +173,22 @@ __host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc)
         L.slab = o;    o = al16(o + (size_t)K * ring_row(M) * 8);
     }
     L.list = o;
+    return L;
+}
+
+// Close calls a wave can note: what the launch leaves of LDS. A launch argument,
+// so that the kernel makes no 64-bit division.
+[[maybe_unused]] inline int tile_list_cap(int M, int K, int W, int acc)
+{
+    const size_t o = mfma_lds(M, K, W, acc).list;
     const size_t left = o < (size_t)kMaxLds ? (size_t)kMaxLds - o : 0;
     const size_t cap = left / ((size_t)W * 8) / 2 * 2;
-    L.list_cap = cap > (size_t)kMaxList ? kMaxList : (int)cap;
-    L.total = o + (size_t)W * L.list_cap * 8;
-    return L;
+    return cap > (size_t)kMaxList ? kMaxList : (int)cap;
+}
+
+[[maybe_unused]] inline size_t tile_lds_bytes(int M, int K, int W, int acc)
+{
+    return mfma_lds(M, K, W, acc).list + (size_t)W * tile_list_cap(M, K, W, acc) * 8;
 }
 
 // Orders this wave's LDS accesses of different types (the hardware keeps a
@@ -222,7 +232,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                   int32_t *__restrict__ labels, const int32_t *__restrict__ labels_in,
                   float *__restrict__ min_d2, double *__restrict__ part_sums,
                   int32_t *__restrict__ part_counts, Ctl *__restrict__ ctl, int t, int fixed,
-                  int force64)
+                  int force64, int lcap)
 {
     using TG = TileGeom<M>;
     using SP = Split<M>;
@@ -254,8 +264,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     float *cnorm = reinterpret_cast<float *>(smem + L.cnorm);
     uint32_t *turn = reinterpret_cast<uint32_t *>(smem + L.misc);
     // (object, limit) of the close calls of this wave
-    int2 *list = reinterpret_cast<int2 *>(smem + L.list) + (size_t)wave * L.list_cap;
-    const int lcap = L.list_cap;
+    int2 *list = reinterpret_cast<int2 *>(smem + L.list) + (size_t)wave * lcap;
     double *wslabs = reinterpret_cast<double *>(smem + L.slab) + (size_t)wave * kP * (K + 1) * (M + 1);
 
     // The grid works in rounds of G*W wave tiles; in round r, wave w of
@@ -982,7 +991,8 @@ hipError_t launch_m(const StepArgs &a, Mode mode, const AccumPlan &p, hipStream_
             return hipErrorInvalidConfiguration;                                               \
         LLOYD_STEP_LAUNCH(kern, grid, block, p.lds_bytes, s, a,                                \
                               a.X, a.n, a.C, a.K, a.labels, a.labels_in, a.min_d2,            \
-                              a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64);    \
+                              a.part_sums, a.part_counts, a.ctl, a.t, a.fixed, a.force64,     \
+                              p.list_cap);                                                    \
     } while (0)
     switch (mode) {
     case kAssign: LLOYD_MFMA_LAUNCH(kAssign, 0); break;
@@ -1032,8 +1042,9 @@ namespace {
 int most_waves(int M, int K, int acc)
 {
     for (int w = kMaxWaves; w > 0; --w) {
-        const MfmaLds L = mfma_lds(M, K, w, acc);
-        if (L.total <= (size_t)kMaxLds && (w == 1 || L.list_cap >= kMinList)) return w;
+        if (tile_lds_bytes(M, K, w, acc) <= (size_t)kMaxLds &&
+            (w == 1 || tile_list_cap(M, K, w, acc) >= kMinList))
+            return w;
     }
     return 0;
 }
@@ -1073,7 +1084,8 @@ AccumPlan plan_tile(int64_t n, int M, int K, Mode mode)
     p.waves = W;
     p.groups = (int)groups;
     p.accum = acc;
-    p.lds_bytes = mfma_lds(M, K, W, acc).total;
+    p.list_cap = tile_list_cap(M, K, W, acc);
+    p.lds_bytes = tile_lds_bytes(M, K, W, acc);
     return p;
 }
 
