@@ -94,12 +94,14 @@ __device__ inline void load_tail_tile(const float *__restrict__ X, int64_t n, in
         // lanes past the tile's last float4 read that one again, as in load_tile
         const int idx0 = lane + kWave * v;
         const int idx = idx0 < G::kVec ? idx0 : G::kVec - 1;
-        float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float *s = X + f0 + 4 * idx;
-        if (4 * idx + 0 < nf) r.x = s[0];
-        if (4 * idx + 1 < nf) r.y = s[1];
-        if (4 * idx + 2 < nf) r.z = s[2];
-        if (4 * idx + 3 < nf) r.w = s[3];
+        // clamped into X and zeroed after: loads under a condition each, merged
+        // with zeros, are waited for one by one
+        const int f = 4 * idx, last = nf - 1;
+        const float *s = X + f0;
+        const float x = s[f < last ? f : last], y = s[f + 1 < last ? f + 1 : last];
+        const float z = s[f + 2 < last ? f + 2 : last], w = s[f + 3 < last ? f + 3 : last];
+        const float4 r = make_float4(f < nf ? x : 0.f, f + 1 < nf ? y : 0.f, f + 2 < nf ? z : 0.f,
+                                     f + 3 < nf ? w : 0.f);
         buf[v] = r;
     }
 }

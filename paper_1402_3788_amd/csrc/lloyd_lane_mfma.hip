@@ -351,17 +351,26 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
             xb[b][1] = *reinterpret_cast<const f4u *>(tb + (r0 + 16 * b * M + c1));
         }
     };
-    // guarded form for the last tiles: zero past n and past M
+    // guarded form for the last tiles: zero past n and past M. Clamped into X and
+    // zeroed afterwards: loads under a condition each, merged with zeros, were
+    // waited for one by one.
     auto load_ops_tail = [&](int64_t q, f4v (&xb)[4][2]) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int64_t r = q * kWave + 16 * b + o16;
+            const float *row = X + (r < n ? r : n - 1) * M;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int f = 8 * g + e;
-                xb[b][e / 4][e % 4] = (r < n && f < M) ? X[r * M + f] : 0.f;
+                xb[b][e / 4][e % 4] = row[f < M ? f : M - 1];
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (q * kWave + 16 * b + o16 >= n || 8 * g + e >= M) xb[b][e / 4][e % 4] = 0.f;
     };
     const int jr = j < M ? j : M - 1;
 
@@ -369,17 +378,18 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     // s + 32h of the tile into slab h (two slabs), or of object 2s + h (one
     // slab: objects in ascending order, the two of a step meeting on an
     // address only in the LDS's lane order).
-    // accumulation values of tile q (the guarded form reads zeros past n)
+    // accumulation values of tile q (past n the guarded form reads the last
+    // object, which nothing adds)
     auto load_acc = [&](int64_t q, float (&xa)[32], auto tail) {
         constexpr bool kTail = decltype(tail)::value;
         const float *tb = X + q * (kWave * M);                 // scalar
-        const int c = (S == 2 ? 32 * h : h) * M + jr;
+        const int r0 = S == 2 ? 32 * h : h;
         constexpr int kObjStride = S == 2 ? 1 : 2;
+        const int last = (int)(n - 1 - q * kWave);             // (of the last tile: below 64)
 #pragma unroll
         for (int s = 0; s < 32; ++s) {
-            if (kTail) xa[s] = (q * kWave + (S == 2 ? 32 * h : h) + kObjStride * s < n)
-                                   ? tb[c + kObjStride * s * M] : 0.f;
-            else xa[s] = tb[c + kObjStride * s * M];
+            const int r = r0 + kObjStride * s;
+            xa[s] = tb[(kTail && r > last ? last : r) * M + jr];
         }
     };
 
