@@ -305,9 +305,9 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
             tiles[(i / kSlack) * kSlot + kWave * M + (i % kSlack)] = 0.f;
     }
     if (MODE != kAccumLabels) {
-        constexpr int kBatch = 4;
         const int entries = KT * KC * kWave;
-        for (int i0 = tid; i0 < entries; i0 += kBatch * blockDim.x) {
+        auto build = [&](int i0, auto batch) {
+            constexpr int kBatch = decltype(batch)::value;
             float raw[kBatch][8];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
@@ -342,7 +342,18 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                                         first ? hi[2] : lo[2], first ? hi[3] : lo[3]);
                 }
             }
+        };
+        // (batches of four as far as they go: half-empty ones cost an assignment
+        // of few objects to 256 centres 1 us)
+        const int rounds = (KT * KC + W - 1) / W;
+        int r = 0;
+        for (; r + 4 <= rounds; r += 4)
+            build(tid + r * (int)blockDim.x, std::integral_constant<int, 4>{});
+        if (rounds - r >= 2) {
+            build(tid + r * (int)blockDim.x, std::integral_constant<int, 2>{});
+            r += 2;
         }
+        if (rounds - r > 0) build(tid + r * (int)blockDim.x, std::integral_constant<int, 1>{});
         // |c_k|^2 in fp32, features in order; padding centres (k >= K) get
         // the largest finite norm: their scores stay finite (a packed key of an
         // infinite score would be a NaN)
