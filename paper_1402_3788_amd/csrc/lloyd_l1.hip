@@ -4,7 +4,8 @@
 // formed by the accumulate-from-labels and centres launches shared with the
 // Euclidean path. This kernel serves the assign-only call and the iterations
 // with K > 32; below that an iteration assigns and accumulates in one launch
-// of the direct-form lane kernel (lloyd_lane.hip).
+// of the direct-form lane kernel, but for shapes that leave it few waves and for
+// few objects of many features (plan_lane_l1 in lloyd_lane.hip).
 //
 // One object per lane, on the vector ALU (the L1 distance is no contraction,
 // so there is nothing for the matrix cores). The kernel is compiled for each

@@ -55,8 +55,16 @@ constexpr int kL1 = 1;
 // fused form saves the accumulate launch's second read of X. Measured at
 // M = 25: K = 16, n = 2e6: 75.2 us per L1 iteration against 103.4 for the
 // two-launch form; K = 64, n = 2e7: 2,110 against 1,954.
-constexpr int kL1FusedMinWaves = 8;
-constexpr int kL1FusedMaxK = 32;
+[[maybe_unused]] constexpr int kL1FusedMinWaves = 8;
+[[maybe_unused]] constexpr int kL1FusedMaxK = 32;
+// With few tiles the launch takes as long as one tile's distance loop, and from
+// this many centres of more than 36 features on the two-launch form is
+// shorter: ten iterations at n = 60,000: M = 37, K = 24 265 us (fused 286), K =
+// 32 298 (354); but M = 33, K = 24 256 (215), M = 37, K = 16 243 (248). At n =
+// 150,000, M = 37, K = 20 the fused form is the shorter one again, 293 us (369).
+[[maybe_unused]] constexpr int kL1FewTiles = 6 * kCUs;
+[[maybe_unused]] constexpr int kL1FewTilesK = 20;
+[[maybe_unused]] constexpr int kL1FewTilesM = 37;
 // Sums of a workgroup up to which few tiles are spread (256 rows of 2048
 // sums: 4 MB of partials).
 [[maybe_unused]] constexpr int kSpreadKM = 2048;
@@ -345,45 +353,67 @@ hipError_t LLOYD_PART_FN(launch_lane_l1_part)(const StepArgs &a, const AccumPlan
 }
 
 #if LLOYD_PART == 0
+namespace {
+
+size_t lane_lds(int M, int K, Mode mode, int W, int pa)
+{
+    size_t b = lane_slab_off(M, W);
+    if (mode != kAssign) b += (size_t)W * lane_acc_p(M, pa) * K * (M + 1) * 8;
+    return b;
+}
+
+// Most waves whose state fits in LDS, with slabs for the most objects per step
+// (pa = 0) unless one object per step (pa = 1) leaves more waves.
+int lane_most_waves(int M, int K, Mode mode, int &pa)
+{
+    auto most = [&](int form) {
+        int w = kMaxWaves;
+        while (w > 0 && lane_lds(M, K, mode, w, form) > (size_t)kMaxLds) --w;
+        return w;
+    };
+    const int w0 = most(0), w1 = mode != kAssign ? most(1) : 0;
+    pa = w1 > w0 ? 1 : 0;
+    return pa == 1 ? w1 : w0;
+}
+
+}  // namespace
+
 AccumPlan plan_lane(int64_t n, int M, int K, Mode mode)
 {
     AccumPlan p{};
     p.path = kPathValu;
-    auto bytes = [&](int W, int pa) {
-        size_t b = lane_slab_off(M, W);
-        if (mode != kAssign) b += (size_t)W * lane_acc_p(M, pa) * K * (M + 1) * 8;
-        return b;
-    };
-    auto most_waves = [&](int pa) {
-        int w = kMaxWaves;
-        while (w > 0 && bytes(w, pa) > (size_t)kMaxLds) --w;
-        return w;
-    };
-    // slabs with the most objects per step unless one object per step leaves
-    // more waves
-    int pa = 0, W = most_waves(0);
-    if (mode != kAssign && most_waves(1) > W) {
-        pa = 1;
-        W = most_waves(1);
-    }
+    int pa = 0;
+    int W = lane_most_waves(M, K, mode, pa);
     const int64_t nq = (n + kWave - 1) / kWave;
     while (W > 1 && W / 2 >= nq) W /= 2;
     // few tiles: spread them over the compute units in small workgroups, where
-    // the additional rows of partials are short
-    while (W > 1 && K * M <= kSpreadKM && (nq + W - 1) / W < kCUs) W /= 2;
+    // the additional rows of partials are short and, with the long slab sums of
+    // up to three features aside (16 slabs and more per wave: a run of n =
+    // 110,000, M = 2, K = 4 takes 124 us for ten iterations instead of 131), as
+    // long as every wave keeps to one tile (n = 100,000, K = 4: M = 25 139 us
+    // for ten iterations, 150 with half the waves and two tiles; M = 64 205 and
+    // 323).
+    while (W > 1 && K * M <= kSpreadKM &&
+           (M < 4 ? (nq + W - 1) / W < kCUs : (int64_t)(W / 2) * kCUs >= nq))
+        W /= 2;
     int64_t groups = (nq + W - 1) / W;
     if (groups > kCUs) groups = kCUs;       // one persistent workgroup per compute unit
     p.waves = W;
     p.groups = (int)groups;
     p.accum = pa;
-    p.lds_bytes = bytes(W, pa);
+    p.lds_bytes = lane_lds(M, K, mode, W, pa);
     return p;
 }
 
 AccumPlan plan_lane_l1(int64_t n, int M, int K)
 {
     AccumPlan p = plan_lane(n, M, K, kAssignAccum);
-    if (K > kL1FusedMaxK || (p.waves < kL1FusedMinWaves && p.groups >= kCUs))
+    // by the waves that LDS holds, not by those of a spread plan
+    int pa = 0;
+    const int most = lane_most_waves(M, K, kAssignAccum, pa);
+    const int64_t nq = (n + kWave - 1) / kWave;
+    if (K > kL1FusedMaxK || (most < kL1FusedMinWaves && nq > (int64_t)most * (kCUs - 1)) ||
+        (nq <= kL1FewTiles && K >= kL1FewTilesK && M >= kL1FewTilesM))
         p.waves = 0;   // not used
     return p;
 }

@@ -24,6 +24,8 @@ I, I64 = ctypes.c_int, ctypes.c_int64
 ASSIGN, ASSIGN_ACCUM, ACCUM_LABELS = 0, 1, 2
 MAX_LDS = 160 * 1024
 plan_lane_mfma = _planner("_ZN5lloyd14plan_lane_mfmaEliiNS_4ModeE", AccumPlan, I64, I, I, I)
+plan_lane = _planner("_ZN5lloyd9plan_laneEliiNS_4ModeE", AccumPlan, I64, I, I, I)
+plan_lane_l1 = _planner("_ZN5lloyd12plan_lane_l1Elii", AccumPlan, I64, I, I)
 plan_tile = _planner("_ZN5lloyd9plan_tileEliiNS_4ModeE", AccumPlan, I64, I, I, I)
 lane_mfma_offs_at = _planner("_ZN5lloyd17lane_mfma_offs_atEiii", ctypes.c_size_t, I, I, I)
 
@@ -51,3 +53,23 @@ def test_lists_of_close_calls_fit(mode):
             p = plan_tile(n, M, K, mode)
             assert p.waves >= 1 and p.lds_bytes <= MAX_LDS, (n, M, K)
             assert p.lds_bytes > p.waves * p.list_cap * 8 >= 0
+
+
+@pytest.mark.parametrize("M,K", [(25, 16), (10, 8), (3, 5), (64, 4), (25, 32)])
+def test_l1_runs_of_few_objects_assign_and_sum_in_one_launch(M, K):
+    """A plan spread over the compute units has few waves per workgroup because
+    there are few tiles, not because LDS holds no more."""
+    for n in (1, 5_000, 16_400, 20_000, 60_000, 98_304, 100_000, 150_000, 190_000):
+        p = plan_lane_l1(n, M, K)
+        assert p.waves >= 1, n
+        assert p.waves * p.groups >= min((n + 63) // 64, p.waves * 256)
+
+
+@pytest.mark.parametrize("M,K", [(4, 4), (10, 3), (25, 4), (25, 16), (64, 4)])
+def test_few_tiles_are_spread_in_one_round(M, K):
+    """Smaller workgroups only as long as no wave gets a second tile for it."""
+    full = plan_lane(10**7, M, K, ASSIGN_ACCUM).waves
+    for n in (64, 5_000, 20_000, 65_536, 65_600, 98_304, 98_368, 150_000, 300_000):
+        p = plan_lane(n, M, K, ASSIGN_ACCUM)
+        assert p.waves == full or p.waves * p.groups >= (n + 63) // 64, n
+        assert p.groups <= 256
