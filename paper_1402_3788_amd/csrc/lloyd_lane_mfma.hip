@@ -865,12 +865,14 @@ AccumPlan plan_lane_mfma(int64_t n, int M, int K, Mode mode)
     const int KB = lane_blocks(K);
     int W = mode == kAssign ? assign_waves(KB) : kWaves;
     const int64_t nq = (n + kWave - 1) / kWave;
-    // few tiles: one wave per workgroup rather than eight on one compute unit
-    while (W > 1 && (nq + W - 1) / W < kCUs) W /= 2;
-    int64_t groups = (nq + W - 1) / W;
-    // persistent workgroups
+    // few tiles: smaller workgroups on more compute units rather than eight waves
+    // on one, as long as every wave keeps to one tile (ten iterations, M = 25: K =
+    // 16, n = 40,000 138 us, 149 with eight waves, and at n = 80,000 149, 155
+    // with four waves and two tiles; K = 64, n = 16,000 180 and 200)
     const int64_t most = mode == kAssign ? assign_groups(KB) * kCUs : kCUs;
-    if (groups > most) groups = most;
+    while (W > 1 && W / 2 * most >= nq) W /= 2;
+    int64_t groups = (nq + W - 1) / W;
+    if (groups > most) groups = most;       // persistent workgroups
     p.waves = W;
     p.groups = (int)groups;
     p.accum = 0;

@@ -73,3 +73,14 @@ def test_few_tiles_are_spread_in_one_round(M, K):
         p = plan_lane(n, M, K, ASSIGN_ACCUM)
         assert p.waves == full or p.waves * p.groups >= (n + 63) // 64, n
         assert p.groups <= 256
+
+
+@pytest.mark.parametrize("mode,limit", [(ASSIGN, 768), (ASSIGN_ACCUM, 256), (ACCUM_LABELS, 256)])
+@pytest.mark.parametrize("M,K", [(10, 8), (25, 16), (25, 32), (32, 64)])
+def test_few_tiles_of_the_lane_kernel_are_spread_in_one_round(M, K, mode, limit):
+    full = plan_lane_mfma(10**7, M, K, mode)
+    assert full.groups <= limit
+    for n in (64, 5_000, 16_384, 40_000, 65_536, 70_000, 100_000, 131_072, 131_136, 500_000):
+        p = plan_lane_mfma(n, M, K, mode)
+        assert p.waves == full.waves or p.waves * p.groups >= (n + 63) // 64, n
+        assert p.groups <= full.groups, n
