@@ -141,6 +141,15 @@ __device__ inline double dist_fp64(const float *xs, const float *c)
     return d;
 }
 
+// The reported distance of an object to its centre: +inf where it is not finite
+// (a NaN feature too: no centre is at a finite distance).
+template <int M>
+__device__ inline float reported_d2(const float *xs, const float *c)
+{
+    const double d = dist_fp64<M>(xs, c);
+    return (float)(d < INFINITY ? d : INFINITY);
+}
+
 // Nearest centre by dist_fp64 over all K centres, lowest index on ties.
 template <int M>
 __device__ inline int argmin_fp64(const float *xs, const float *__restrict__ C, int K,

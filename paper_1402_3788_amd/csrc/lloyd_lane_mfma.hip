@@ -685,7 +685,7 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         if (act) {
             labels[i] = lab;
             if (MODE == kAssign && min_d2 != nullptr)
-                min_d2[i] = (float)dist_fp64<M>(x, C + (int64_t)lab * M);
+                min_d2[i] = reported_d2<M>(x, C + (int64_t)lab * M);
             if (kAcc) {
                 // one lane per object into the wave's slab of the object's
                 // tile half: the LDS applies the lanes of an add in a fixed

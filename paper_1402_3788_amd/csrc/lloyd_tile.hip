@@ -705,7 +705,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     auto store_label = [&](const float (&x)[M], int i, int lab, int mark) {
         labels[i] = lab ^ mark;
         if (MODE == kAssign && min_d2 != nullptr)
-            min_d2[i] = (float)dist_fp64<M>(x, C + (int64_t)lab * M);
+            min_d2[i] = reported_d2<M>(x, C + (int64_t)lab * M);
     };
     int first[kMaxWaves + 1];      // list position of each wave's first object
     first[0] = 0;

@@ -111,3 +111,20 @@ def test_farthest_init_with_nonfinite_objects_follows_the_oracle(case):
     got, _ = km.kmeans_init_farthest(torch.from_numpy(X).to(DEV), K)
     got = got.cpu().numpy().ravel() if hasattr(got, "cpu") else np.asarray(got).ravel()
     assert np.array_equal(got[:K], want[:K])
+
+
+@pytest.mark.parametrize("path", ["direct", "mfma", "tiles"])
+@pytest.mark.parametrize("K", [3, 16, 40, 64])
+def test_distance_of_a_nonfinite_object_is_infinite(K, path):
+    """As the oracle reports it: no centre is at a finite distance."""
+    print(f"[nonfinite d2] K={K} path={path}", flush=True)
+    rng = np.random.default_rng(K)
+    C = rng.standard_normal((K, 25)).astype(np.float32)
+    X = rng.standard_normal((1001, 25)).astype(np.float32)
+    X[3, 4], X[7, 0], X[9, 24], X[1000] = np.nan, np.inf, -np.inf, np.nan
+    want, d1, _ = oracle.assign(X, C, with_dist=True)
+    lab, d2 = km.kmeans_assign(torch.from_numpy(X).to(DEV), torch.from_numpy(C).to(DEV),
+                               with_min_d2=True, path=path)
+    assert np.array_equal(lab.cpu().numpy(), want)
+    assert np.isinf(d1[[3, 7, 9, 1000]]).all()
+    np.testing.assert_allclose(d2.cpu().numpy(), d1, rtol=27 * 2.0**-22, atol=1e-30)
