@@ -29,11 +29,15 @@
 //      lane l with the two best keys of object l; a label is accepted when the
 //      two differ by more than twice the proven error bound thr/2. The others
 //      (close calls) are noted in a list in LDS and decided after the wave's
-//      last tile, 64 at a time, one object per lane: direct-form fp32 distances
-//      to every centre, whose error is relative to the distance itself
-//      (gamma_{M+1}) and not to the norms, and fp64 distances in the reference
-//      operation order (lowest index on ties) where those leave a gap below
-//      4 gamma_{M+2}. Every label is the exact-arithmetic argmin;
+//      last tile, in columns of 16: their scores are formed again, and fp64
+//      distances in the reference operation order (lowest index on ties) to
+//      the centres within the bound of the best score decide. Where those are
+//      many (a guard band wide against the distances between the centres),
+//      with one block, and with two and many close calls, they are decided 64
+//      at a time, one object per lane: direct-form fp32 distances to every
+//      centre, whose error is relative to the distance itself (gamma_{M+1})
+//      and not to the norms, and fp64 distances to those that this leaves
+//      within 4 gamma_{M+2}. Every label is the exact-arithmetic argmin;
 //   5. accumulation (the numerator and denominator of Eq. (1)): lane l
 //      writes the slab row offset of object l to the wave's offset table;
 //      lanes (h, .) read the offsets of their 32 objects back with broadcast
@@ -77,6 +81,13 @@
 // took 360 of 459 us of an assignment with a third of its objects close (n = 2e6,
 // M = 25, K = 64, random initial centres), and their code in the loop cost the
 // launches without any close call 2 %.
+//
+// Why columns and candidates: the direct form over all centres for every close
+// call made a wave that has a few of them wait for K distances in sequence and,
+// where one is tied, for K fp64 distances. Assignment, M = 25, K = 64: n = 70,000,
+// random initial centres 37 us, now 12.3; n = 2e6 84 and 52; ties (small whole
+// numbers), n = 300,000 49 and 17.5; one object with a NaN, n = 4,000 35 and 8.9.
+// A run of n = 2e6 from random centres, five iterations: 557 us, now 443.
 #include "lloyd.h"
 #include "lloyd_device.h"
 
@@ -105,11 +116,12 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kWaves = 8;
 constexpr int kMinWavesPerSimd = 2;   // caps registers at 256 per lane
 // An assignment holds no accumulation values: four waves per SIMD with one
-// block (two workgroups of eight waves on a compute unit), three with more
-// (three workgroups of four waves; at four 94 registers spilled).
-__host__ __device__ constexpr int assign_waves_per_simd(int KB) { return KB == 1 ? 4 : 3; }
-__host__ __device__ constexpr int assign_waves(int KB) { return KB == 1 ? 8 : 4; }
-__host__ __device__ constexpr int assign_groups(int KB) { return KB == 1 ? 2 : 3; }   // per compute unit
+// block (two workgroups of eight waves on a compute unit), three with two
+// (three workgroups of four), two with four (at three the hot loop spilled:
+// 28.1 us for n = 500,000, M = 25, K = 64, now 16.6).
+__host__ __device__ constexpr int assign_waves_per_simd(int KB) { return KB == 1 ? 4 : KB == 2 ? 3 : 2; }
+[[maybe_unused]] __host__ __device__ constexpr int assign_waves(int KB) { return KB == 2 ? 4 : 8; }
+__host__ __device__ constexpr int assign_groups(int KB) { return KB == 1 ? 2 : KB == 2 ? 3 : 1; }   // per compute unit
 constexpr int kMaxMLane = 32;         // features: four lane groups of eight
 [[maybe_unused]] constexpr int kMaxKLane = 64;   // centres: up to four 16-row A operands
 
@@ -162,6 +174,10 @@ __host__ __device__ constexpr bool lane_a_in_lds(int KB) { return KB > 1; }
 // K = 64 21.0 us instead of 18.0.
 constexpr size_t kStaticLds = 64;       // the waves' counts
 constexpr int kMaxList = 2048;
+// Candidates per lane (a quarter of the centres) up to which fp64 distances to
+// them decide a close call; more mean a guard band wide against the distances
+// between the centres, which the direct fp32 form mostly resolves.
+[[maybe_unused]] __host__ __device__ constexpr int max_cand(int M) { return M <= 8 ? 16 : 4; }
 [[maybe_unused]] inline int lane_list_cap(int M, int K, int W, Mode mode)
 {
     if (mode == kAccumLabels) return 0;
@@ -477,6 +493,7 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     constexpr float kE = 3.02f * 1.5258789e-05f + 104.0f * 1.1920929e-07f + 1.01f * kKeyRel;
     constexpr uint32_t kIdxMask = (1u << kBits) - 1u;
     constexpr uint32_t kKeyMask = ~kIdxMask;
+    constexpr int kMaxCand = max_cand(M);
 
     int ncl = 0;             // close calls of this wave
 
@@ -649,10 +666,9 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         step(q, xb[0], xa[0], xb[kOpSets - 1], xa[kLateAcc ? 0 : 1], q, std::true_type{});
     }
 
-    // ---- the close calls: lane l decides object i
-    auto decide = [&](bool act, int i) {
+    // ---- the close calls: lane l's object i (act lanes are the first of the wave)
+    auto load_row = [&](int i, float (&x)[M]) {
         const float *xr = X + (int64_t)i * M;
-        float x[M];
 #pragma unroll
         for (int f = 0; f + 4 <= M; f += 4) {
             const f4v v = *reinterpret_cast<const f4u *>(xr + f);
@@ -661,31 +677,166 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         }
 #pragma unroll
         for (int f = M / 4 * 4; f < M; ++f) x[f] = xr[f];
-        constexpr float kTau = 4.0f * (float)(M + 2) * 5.9604645e-8f;
-        float b1 = INFINITY, b2 = INFINITY;
+    };
+    bool wide = false;       // (uniform) straight to the direct form
+    auto decide = [&](bool act, int i) {
         int lab = 0;
-        if (!force64)
-            for (int k = 0; k < K; ++k) {
+        float dmin = 0.f;
+        bool open = act;
+        const uint64_t actm = __ballot(act);
+#pragma unroll 1
+        for (int c = 0; c < 4 && !force64 && !wide; ++c) {
+            if (((actm >> (16 * c)) & 0xffffull) == 0ull) break;
+            // column c: the four lanes (g, o16) of object 16c + o16
+            const int ic = __shfl(i, 16 * c + o16, kWave);
+            const bool ac = ((actm >> (16 * c + o16)) & 1ull) != 0ull;
+            const float *xr = X + (int64_t)ic * M;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = xr[8 * g + e < M ? 8 * g + e : M - 1];
+            float x[M];
+            load_row(ic, x);
+            float xsq = 0.f;
+            int bad = 0;                       // a NaN or an infinite feature
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[e] = 8 * g + e < M ? v[e] : 0.f;
+                xsq = __builtin_fmaf(v[e], v[e], xsq);
+                bad |= fabsf(v[e]) < INFINITY ? 0 : 1;
+            }
+            uint32_t vh[4], vl[4];
+            split_bf16x8(v, vh, vl);
+            f4v d[KB];
+            float best = INFINITY;
+#pragma unroll
+            for (int cb = 0; cb < KB; ++cb) {
+                uint32_t h4[4], l4[4];
+                a_ops(cb, h4, l4, d[cb]);
+                d[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(l4), as_bf8(vh), d[cb], 0, 0, 0);
+                d[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(h4), as_bf8(vl), d[cb], 0, 0, 0);
+                d[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(h4), as_bf8(vh), d[cb], 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) best = fminf(best, d[cb][r]);
+            }
+#pragma unroll
+            for (int m = 16; m <= 32; m <<= 1) {
+                best = fminf(best, __shfl_xor(best, m, kWave));
+                xsq = xsq + __shfl_xor(xsq, m, kWave);
+                bad |= __shfl_xor(bad, m, kWave);
+            }
+            // a centre whose score is above the best by more than twice the
+            // bound is not the nearest; a NaN score or limit keeps the centre
+            const float lim = best + (2.02f * kE * (3.02f * cmax + 1.0001f * xsq) + 1e-30f);
+            uint32_t mask = 0u;
+#pragma unroll
+            for (int cb = 0; cb < KB; ++cb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    mask |= !(d[cb][r] > lim) && 16 * cb + 4 * g + r < K ? 1u << (4 * cb + r) : 0u;
+            // an object at no finite distance from any centre has label 0
+            if (bad != 0) mask = g == 0 ? 1u : 0u;
+            int most = __popc(mask);
+#pragma unroll
+            for (int m = 16; m <= 32; m <<= 1) {
+                const int om = __shfl_xor(most, m, kWave);
+                most = om > most ? om : most;
+            }
+            const bool few = ac && most >= 1 && most <= kMaxCand;
+            wide = wide || __popcll(__ballot(ac && most > kMaxCand)) >= kWave / 4;
+            double bd = INFINITY;
+            int lc = 0;
+            for (uint32_t m = few ? mask : 0u; __ballot(m != 0u) != 0ull; m &= m - 1u) {
+                if (m == 0u) continue;
+                const int bit = __builtin_ctz(m);
+                const int k = 16 * (bit >> 2) + 4 * g + (bit & 3);       // ascending
+                double dk;
+                if constexpr (MODE == kAssign) dk = dist_fp64<M>(x, ctab + k * M);
+                else dk = dist_fp64<M>(x, C + k * M);
+                if (dk < bd) {
+                    bd = dk;
+                    lc = k;
+                }
+            }
+#pragma unroll
+            for (int m = 16; m <= 32; m <<= 1) {
+                const double od = __shfl_xor(bd, m, kWave);
+                const int ol = __shfl_xor(lc, m, kWave);
+                if (od < bd || (od == bd && ol < lc)) {
+                    bd = od;
+                    lc = ol;
+                }
+            }
+            // lane (c, o16) owns the object; one whose candidates hold no
+            // finite distance stays open
+            if (g == c) {
+                lab = lc;
+                dmin = (float)bd;                      // (+inf with label 0)
+                open = ac && !(few && (bad != 0 || bd < INFINITY));
+            }
+        }
+        const bool late = __ballot(open) != 0ull;
+        float x[M];
+        if (kAcc || late) load_row(i, x);
+        if (late) {
+            // the direct fp32 form over all centres, whose error is relative to
+            // the distance, and fp64 among the centres that it leaves in
+            // question. An object with a NaN or an infinity is at no finite
+            // distance from any centre: label 0.
+            constexpr float kTau = 4.0f * (float)(M + 2) * 5.9604645e-8f;
+            bool finite = true;
+#pragma unroll
+            for (int f = 0; f < M; ++f) finite = finite && fabsf(x[f]) < INFINITY;
+            auto direct = [&](int k) {
                 float d = 0.f;
 #pragma unroll
                 for (int f = 0; f < M; ++f) {
                     const float e = x[f] - C[k * M + f];
                     d = __builtin_fmaf(e, e, d);
                 }
-                const bool lt = d < b1;
-                b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
-                b1 = lt ? d : b1;
-                lab = lt ? k : lab;
+                return d;
+            };
+            float b1 = INFINITY, b2 = INFINITY;
+            int ld = 0;
+            if (!force64)
+                for (int k = 0; k < K; ++k) {
+                    const float d = direct(k);
+                    const bool lt = d < b1;
+                    b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
+                    b1 = lt ? d : b1;
+                    ld = lt ? k : ld;
+                }
+            const bool sure = !force64 && ((K == 1) || (b2 - b1 > kTau * b2 && b2 >= 1e-30f));
+            const bool unsure = open && !sure && finite;
+            if (__ballot(unsure) != 0ull) {
+                uint64_t mask = force64 ? ~0ull >> (64 - K) : 0ull;
+                if (!force64)
+                    for (int k = 0; k < K; ++k) {
+                        const float d = direct(k);
+                        // (a NaN or an overflowed distance stays in question)
+                        mask |= !(d - b1 > kTau * d && d >= 1e-30f) ? 1ull << k : 0ull;
+                    }
+                if (unsure) {
+                    double bd = INFINITY;
+                    ld = 0;
+                    for (uint64_t m = mask; m != 0ull; m &= m - 1ull) {
+                        const int k = __builtin_ctzll(m);
+                        const double dk = dist_fp64<M>(x, C + k * M);
+                        if (dk < bd) {
+                            bd = dk;
+                            ld = k;
+                        }
+                    }
+                }
             }
-        const bool sure = !force64 && ((K == 1) || (b2 - b1 > kTau * b2 && b2 >= 1e-30f));
-        if (act && !sure) {
-            double bd;
-            lab = argmin_fp64<M>(x, C, K, bd);
+            if (open) {
+                lab = finite ? ld : 0;
+                if (MODE == kAssign && min_d2 != nullptr)
+                    dmin = reported_d2<M>(x, C + (int64_t)lab * M);
+            }
         }
         if (act) {
             labels[i] = lab;
-            if (MODE == kAssign && min_d2 != nullptr)
-                min_d2[i] = reported_d2<M>(x, C + (int64_t)lab * M);
+            if (MODE == kAssign && min_d2 != nullptr) min_d2[i] = dmin;
             if (kAcc) {
                 // one lane per object into the wave's slab of the object's
                 // tile half: the LDS applies the lanes of an add in a fixed
@@ -718,8 +869,8 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
     // (unlikely: the code below is laid out behind the sums)
     if (kDist && __builtin_expect(all > 0, 0)) {
         // The close calls of the workgroup's waves, one list after the other,
-        // in batches of 64 dealt to the waves in turn: a wave alone rarely has
-        // a full batch, and a batch costs the same for one object as for 64.
+        // in batches of 64 (16 or 32 where that gives every wave one) dealt to
+        // the waves in turn: a wave alone rarely has a full batch.
         int first[kWaves + 1];
         first[0] = 0;
 #pragma unroll
@@ -727,8 +878,13 @@ lane_mfma_kernel(const float *__restrict__ X, int64_t n, const float *__restrict
         const int total = __builtin_amdgcn_readfirstlane(first[kWaves]);
         // one add per workgroup: adds of 2048 waves to one word take 20 us
         if (ctl != nullptr && threadIdx.x == 0) atomicAdd(&ctl->fallbacks, all);
-        for (int p0 = wave * kWave; p0 < total; p0 += W * kWave) {
-            const bool act = p0 + lane < total;
+        // The columns' cost does not depend on K, the direct form's does, and is
+        // the lower one with up to 16 centres, or up to 32 and several batches
+        // per wave (n = 2e6, M = 25, K = 20, five iterations 334 us, 388)
+        wide = KB == 1 || (KB == 2 && total > 32 * W);
+        const int per = wide || total > 32 * W ? kWave : total > 16 * W ? 32 : 16;
+        for (int p0 = wave * per; p0 < total; p0 += W * per) {
+            const bool act = lane < per && p0 + lane < total;
             const int p = act ? p0 + lane : p0;
             int w = 0, base = 0;
 #pragma unroll
