@@ -163,7 +163,7 @@ __host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc)
     size_t o = 0;
     L.abf = o;     o = al16(o + (size_t)KT * a_operands(M) * kWave * 16);
     L.cnorm = o;   o = al16(o + (size_t)KT * 16 * 4);
-    L.misc = o;    o = al16(o + 16);
+    L.misc = o;    o = al16(o + 4 * (size_t)(2 * W + 1));  // the turn, the waves' counts and votes
     L.tiles = o;   o = al16(o + (size_t)W * L.tile_floats * 4);
     if (acc == kAccWave || acc == kAccWave1) {
         // one row more than there are clusters takes the adds of close calls
@@ -729,14 +729,13 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
         // rarely has many, and a column costs a quarter of a tile or more).
         // The four lanes (g, l16) of an object hold its features and find the
         // candidates among their own centre rows.
-        int *wcount = reinterpret_cast<int *>(tiles);
-        __syncthreads();
-        if (lane == 0) wcount[wave * kSlot] = ncl;
+        int *wcount = reinterpret_cast<int *>(smem + L.misc) + 1;
+        if (lane == 0) wcount[wave] = ncl;
         __syncthreads();
         int all = 0, batches = 0;
 #pragma unroll
         for (int w = 0; w < kMaxWaves; ++w) {
-            const int c = w < W ? wcount[w * kSlot] : 0;
+            const int c = w < W ? wcount[w] : 0;
             all += c;
             if (c > lcap) {
                 batches += (c + kWave - 1) / kWave;
@@ -746,7 +745,6 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
         }
         total = __builtin_amdgcn_readfirstlane(first[kMaxWaves]);
         over = __builtin_amdgcn_readfirstlane(over);
-        __syncthreads();               // the slots may be used again
         const int columns = (total + 15) / 16;
         batches += columns;
         // one add per workgroup: adds of 2048 waves to one word take 20 us
