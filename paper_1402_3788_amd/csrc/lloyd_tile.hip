@@ -97,6 +97,9 @@ constexpr int kAccWave1 = 3;   // one slab per wave, WaveAcc<M>::Pmax objects pe
 constexpr int kMaxWaves = 8;
 [[maybe_unused]] constexpr int kMinWaveForm = 6;   // fewest waves the wave form is used with
 
+// Candidates of an object in one lane (a quarter of the centres) up to which
+// fp64 distances to them decide; more are mostly resolved by the direct form.
+constexpr int kManyCand = 16;
 constexpr int kMaxList = 4096;     // noted close calls per wave, at most
 // ... and at least, where the choice of waves allows it: a quarter of the 977
 // objects of a wave at n = 2e6
@@ -677,30 +680,59 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     };
     // label of the lane's object x (open lanes) by the direct form over all
     // centres: each fp32 distance is within gamma_{M+1} of the exact one, and
-    // fp64 over all centres decides where that leaves it open
+    // fp64 among the centres that this leaves within 4 gamma_{M+2} of the best
+    // decides where there are several. An object with a NaN or an infinity is
+    // at no finite distance from any centre: label 0.
+    auto is_finite = [&](const float (&x)[M]) {
+        bool f = true;
+#pragma unroll
+        for (int j = 0; j < M; ++j) f = f && fabsf(x[j]) < INFINITY;
+        return f;
+    };
     auto direct = [&](const float (&x)[M], bool open) -> int {
         constexpr float kTau = 4.0f * (float)(M + 2) * 5.9604645e-8f;
+        auto dist = [&](int k) {
+            float d = 0.f;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const float e = x[j] - C[k * M + j];
+                d = __builtin_fmaf(e, e, d);
+            }
+            return d;
+        };
         float b1 = INFINITY, b2 = INFINITY;
         int ld = 0;
         if (!force64)
+#pragma unroll (M <= 16 ? 4 : 1)
             for (int k = 0; k < K; ++k) {
-                float d = 0.f;
-#pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    const float e = x[j] - C[k * M + j];
-                    d = __builtin_fmaf(e, e, d);
-                }
+                const float d = dist(k);
                 const bool lt = d < b1;
                 b2 = __builtin_amdgcn_fmed3f(b1, b2, d);
                 b1 = lt ? d : b1;
                 ld = lt ? k : ld;
             }
         const bool sure = !force64 && ((K == 1) || (b2 - b1 > kTau * b2 && b2 >= 1e-30f));
-        if (open && !sure) {
-            double bd;
-            ld = argmin_fp64<M>(x, C, K, bd);
+        const bool unsure = open && !sure && is_finite(x);
+        if (__ballot(unsure) != 0ull) {
+            double bd = INFINITY;
+            int l64 = 0;
+            for (int k = 0; k < K; ++k) {
+                bool in = unsure;
+                if (!force64) {
+                    const float d = dist(k);
+                    // (a NaN or an overflowed distance stays in question)
+                    in = unsure && !(d - b1 > kTau * d && d >= 1e-30f);
+                }
+                if (__ballot(in) == 0ull) continue;
+                const double dk = dist_fp64<M>(x, C + (int64_t)k * M);
+                if (in && dk < bd) {
+                    bd = dk;
+                    l64 = k;
+                }
+            }
+            ld = unsure ? l64 : ld;
         }
-        return ld;
+        return is_finite(x) ? ld : 0;
     };
     auto store_label = [&](const float (&x)[M], int i, int lab, int mark) {
         labels[i] = lab ^ mark;
@@ -747,29 +779,70 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
         over = __builtin_amdgcn_readfirstlane(over);
         const int columns = (total + 15) / 16;
         batches += columns;
+        // features of a column's objects, the four lanes of each holding them
+        // all, and their operands
+        auto load_column = [&](int i, float (&x)[M], uint32_t (&bop)[kB][4]) {
+            load_row(i, x);
+            wave_sync();
+            if (g == 0)
+#pragma unroll
+                for (int j = 0; j < M; ++j) tile[l16 * M + j] = x[j];
+            wave_sync();
+            b_column(tile + l16 * M, bop);
+        };
         // one add per workgroup: adds of 2048 waves to one word take 20 us
         if (ctl != nullptr && tid == 0 && all > 0) {
             atomicAdd(&ctl->fallbacks, all);
             atomicAdd(&ctl->reruns, batches);
         }
-        for (int col = wave; col < columns; col += W) {
+        // Where the guard band is wide against the distances between the
+        // centres (clusters far from the origin), most centres are candidates,
+        // and the direct form, one object per lane, is the shorter way (n =
+        // 300,000, M = 25, K = 256, offset 20 times the spread: 200 us, 640
+        // column by column): a wave that meets such a column takes its columns
+        // four at a time from then on. A column's sums have the same turn and
+        // order either way.
+        bool wide = force64 != 0;       // (uniform)
+        for (int col = wave; col < columns;) {
+            if (wide) {
+                const int mine = col + g * W;               // lane (g, l16): object l16 of it
+                const int p = 16 * mine + l16;
+                const bool act = p < total;
+                const int i = entry(act ? p : 16 * col)->x;
+                float x[M];
+                load_row(i, x);
+                const int lab = direct(x, act);
+                if (act) store_label(x, i, lab, 0);
+                for (int c = 0; kAcc != 0 && c < 4 && col + c * W < columns; ++c) {
+                    const uint32_t want = ring_seq * (uint32_t)W + (uint32_t)(col + c * W);
+                    if (kAcc == kAccRing && ring_ok) ring_ok = ring_wait(turn, want);
+                    if (act && g == c) {
+                        double *row = kWaveForm
+                            ? wslabs + (size_t)lab * (M + 1)
+                            : reinterpret_cast<double *>(smem + L.slab) + (int64_t)lab * ring_row(M);
+#pragma unroll
+                        for (int j = 0; j < M; ++j)
+                            __hip_atomic_fetch_add(row + j, (double)x[j], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(row + M, 1.0, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    if (kAcc == kAccRing) ring_pass(turn, want + 1);
+                }
+                col += 4 * W;
+                continue;
+            }
             const int p = 16 * col + l16;
             const bool act = p < total;
             const int2 e = *entry(act ? p : 16 * col);
             const int i = e.x;
             const float lim = act ? __int_as_float(e.y) : -INFINITY;
             float x[M];
-            load_row(i, x);
+            uint32_t bop[kB][4];
+            load_column(i, x, bop);
             int lab = 0;
-            bool open = act;
-            if (!force64) {
-                wave_sync();
-                if (g == 0)
-#pragma unroll
-                    for (int j = 0; j < M; ++j) tile[l16 * M + j] = x[j];
-                wave_sync();
-                uint32_t bop[kB][4];
-                b_column(tile + l16 * M, bop);
+            bool open;
+            {
                 // up to four candidates of this lane, 16 bits each
                 uint64_t cand = 0;
                 int nc = 0;
@@ -801,16 +874,59 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                             nc += in ? 1 : 0;
                         }
                 }
+                int most = nc, some = nc;
+#pragma unroll
+                for (int m = 16; m <= 32; m <<= 1) {
+                    const int om = __shfl_xor(most, m, kWave);
+                    most = om > most ? om : most;
+                    some += __shfl_xor(some, m, kWave);
+                }
+                // (an object that is not finite has every centre for a candidate)
+                bool finite = true;
+                open = false;
+                bool many = false;
+                if (__ballot(act && (most > 4 || some == 0)) != 0ull) {
+                    finite = is_finite(x);
+                    open = act && finite && (most > kManyCand || some == 0);
+                    many = act && finite && most > 4 && most <= kManyCand;
+                    if (__popcll(__ballot(open)) >= kWave / 4) {
+                        wide = true;
+                        continue;              // this column too
+                    }
+                }
                 double bd = INFINITY;
-                for (int u = 0; u < (nc < 4 ? nc : 4); ++u) {
-                    const int k = (int)((cand >> (16 * u)) & 0xffffu);
+                auto consider = [&](int k, bool take) {
                     const double dk = dist_fp64<M>(x, C + (int64_t)k * M);
-                    if (dk < bd || (dk == bd && dk < INFINITY && k < lab)) {
+                    if (take && (dk < bd || (dk == bd && dk < INFINITY && k < lab))) {
                         bd = dk;
                         lab = k;
                     }
+                };
+                if (finite && most <= 4)
+                    for (int u = 0; u < nc; ++u)
+                        consider((int)((cand >> (16 * u)) & 0xffffu), true);
+                if (__ballot(many) != 0ull) {
+                    // more than the four that were kept: the scores once more,
+                    // the candidates' distances as they turn up
+                    for (int tt = 0; tt < KT; tt += 2) {
+                        load_ops(tt, o[0]);
+                        load_ops(tt + 1, o[1]);
+                        f4v d[2];
+                        chain_pair(o, bop, d);
+                        uint32_t in = 0u;
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                in |= many && !(d[u][r] > lim) && (tt + u) * 16 + 4 * g + r < K
+                                          ? 1u << (4 * u + r) : 0u;
+                        for (; __ballot(in != 0u) != 0ull; in &= in - 1u) {
+                            const int bit = in != 0u ? __builtin_ctz(in) : 0;
+                            consider(in != 0u ? (tt + (bit >> 2)) * 16 + 4 * g + (bit & 3) : 0,
+                                     in != 0u);
+                        }
+                    }
                 }
-                int most = nc, some = nc;
 #pragma unroll
                 for (int m = 16; m <= 32; m <<= 1) {
                     const double od = __shfl_xor(bd, m, kWave);
@@ -819,11 +935,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                         bd = od;
                         lab = ol;
                     }
-                    const int om = __shfl_xor(most, m, kWave);
-                    most = om > most ? om : most;
-                    some += __shfl_xor(some, m, kWave);
                 }
-                open = act && (most > 4 || some == 0);
             }
             if (__ballot(open) != 0ull) {
                 const int ld = direct(x, open);
@@ -857,6 +969,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
                 }
                 if (kAcc == kAccRing) ring_pass(turn, want + 1);
             }
+            col += W;
         }
         // A list that overflowed is not used: its wave's tiles are read again
         // for marked labels, through a buffer of 128 objects (the list's
