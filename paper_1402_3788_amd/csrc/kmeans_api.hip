@@ -58,11 +58,13 @@ int select_path(int32_t M, int32_t K, uint32_t flags)
 
 // Whether the default path of a shape with many centres assigns and sums in two
 // launches: the fused tile kernel holds the centre operands and the K x M fp64
-// sums in LDS, and with fewer than five waves beside them (K = 384, M = 32: one;
+// sums in LDS, and with fewer than four waves beside them (K = 384, M = 32: one;
 // K = 1024, M = 16: none) the SIMDs idle, while the assigning launch alone
-// keeps its waves. n = 262147, M = 16, K = 1024: 2,926 us per iteration on the
-// vector ALU, the only path that fitted.
-constexpr int kMinFusedWaves = 5;
+// keeps its waves. Five iterations of n = 400,000, fused and in two launches:
+// with four waves M = 37, K = 200 314 and 399 us, M = 57, K = 100 345 and 457, M =
+// 50, K = 140 341 and 374 (n = 100,000 210 and 187); with three M = 57, K = 140
+// 428 and 473, at n = 100,000 251 and 249; with two M = 41, K = 250 1,485 and 473.
+constexpr int kMinFusedWaves = 4;
 
 bool use_split(int32_t M, int32_t K, uint32_t flags)
 {

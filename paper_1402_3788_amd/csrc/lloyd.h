@@ -112,7 +112,7 @@ struct AccumPlan {
 AccumPlan plan_lane(int64_t n, int M, int K, Mode mode);
 AccumPlan plan_lane_mfma(int64_t n, int M, int K, Mode mode);
 AccumPlan plan_tile(int64_t n, int M, int K, Mode mode);
-// The accumulating launch of kPathSplit (accum: its feature slices).
+// The accumulating launch of kPathSplit (accum: features of a slice).
 AccumPlan plan_accum(int64_t n, int M, int K);
 // Waves per workgroup of the tile kernel (0: its state does not fit in LDS).
 int tile_waves(int M, int K, Mode mode);

@@ -128,3 +128,22 @@ def test_sums_from_labels_follow_the_oracle(n, M, K):
         assert np.array_equal(cnt.cpu().numpy(), ocnt)
         scale = np.maximum(np.abs(oC).max(axis=1, keepdims=True), 1e-30)
         assert (np.abs(C.cpu().numpy().astype(np.float64) - oC) <= 2.0**-23 * scale).all()
+
+
+@pytest.mark.parametrize("n,M,K", [(40_007, 57, 140), (40_007, 50, 200), (65_600, 33, 300),
+                                   (20_003, 61, 100), (40_001, 64, 20), (40_000, 48, 100),
+                                   (30_011, 25, 512), (65, 64, 17)])
+def test_sums_in_slices_of_eight_and_sixteen_features(n, M, K):
+    """Whole slices and remainders of every kind (9, 2, 1, 13 features, none)."""
+    print(f"[slices] n={n} M={M} K={K}", flush=True)
+    rng = np.random.default_rng(n + M)
+    X = rng.uniform(-60, 60, (n, M)).astype(np.float32)
+    lab = rng.integers(-1, K + 1, n).astype(np.int32)
+    prev = rng.standard_normal((K, M)).astype(np.float32)
+    C, cnt = km.kmeans_update(torch.from_numpy(X).to(DEV), torch.from_numpy(lab).to(DEV), K,
+                              torch.from_numpy(prev).to(DEV))
+    keep = (lab >= 0) & (lab < K)
+    oC, ocnt = oracle.update(X[keep], lab[keep], K, prev)
+    assert np.array_equal(cnt.cpu().numpy(), ocnt)
+    scale = np.maximum(np.abs(oC).max(axis=1, keepdims=True), 1e-30)
+    assert (np.abs(C.cpu().numpy().astype(np.float64) - oC) <= 2.0**-23 * scale).all()

@@ -84,3 +84,20 @@ def test_few_tiles_of_the_lane_kernel_are_spread_in_one_round(M, K, mode, limit)
         p = plan_lane_mfma(n, M, K, mode)
         assert p.waves == full.waves or p.waves * p.groups >= (n + 63) // 64, n
         assert p.groups <= full.groups, n
+
+
+def test_sums_in_slices_fill_the_chip_within_lds():
+    """Slices of 16, 8 or 4 features with the slabs of at least six waves, but
+    where four features are all that fits."""
+    plan_accum = _planner("_ZN5lloyd10plan_accumElii", AccumPlan, I64, I, I)
+    for M, K in [(16, 1024), (15, 1000), (25, 400), (25, 655), (37, 200), (57, 140), (64, 20), (64, 256)]:
+        for n in (1, 65, 16_384, 400_000, 10**7):
+            p = plan_accum(n, M, K)
+            assert p.accum in (4, 8, 16) and p.lds_bytes <= MAX_LDS and 1 <= p.groups <= 256
+            slices = -(-M // p.accum)
+            assert (p.groups - 1) * slices < 256
+            if p.accum > 4:
+                assert p.waves >= 6 and p.accum // 2 < M
+                assert slices * -(-n // (64 * p.waves)) >= 256
+    assert plan_accum(400_000, 57, 140).accum == 16
+    assert plan_accum(16_384, 25, 400).accum == 4
