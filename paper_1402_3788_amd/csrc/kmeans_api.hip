@@ -73,9 +73,26 @@ bool use_split(int32_t M, int32_t K, uint32_t flags)
     return tile_waves(M, K, kAssignAccum) < kMinFusedWaves && tile_waves(M, K, kAssign) >= 2;
 }
 
+// Sums from labels on the tile path: the tile kernel, whose waves read whole
+// rows, or the launch that takes the features in slices: always with 64
+// features, whose rows the slices share in whole lines, and from 48 on where the
+// tile kernel's waves would take turns and X stays in the last-level cache
+// (256 MB) for the second slice. A kmeans_update by tiles and in slices: n =
+// 400,000: M = 41, K = 64 36.1 and 42.0 us, M = 50, K = 48 40.3 and 33.2, M = 57, K =
+// 64 44.6 and 33.3, M = 64, K = 32 58.6 and 33.2; n = 2e6: M = 50, K = 48 134 and 148,
+// M = 57, K = 64 144 and 170, M = 64, K = 64 202 and 139.
+constexpr int64_t kSlicesBytes = 200'000'000;
+
+bool sum_in_slices(int64_t n, int32_t M, int32_t K)
+{
+    return M >= 64 || (M >= 48 && n * M * 4 <= kSlicesBytes && tile_sums_in_turn(M, K));
+}
+
 AccumPlan plan_for(int p, int64_t n, int32_t M, int32_t K, Mode mode)
 {
-    if (p == kPathTile) return plan_tile(n, M, K, mode);
+    if (p == kPathTile)
+        return mode == kAccumLabels && sum_in_slices(n, M, K) ? plan_accum(n, M, K)
+                                                           : plan_tile(n, M, K, mode);
     if (p == kPathLaneMfma) return plan_lane_mfma(n, M, K, mode);
     return plan_lane(n, M, K, mode);
 }
@@ -136,7 +153,9 @@ Layout layout(int64_t n, int32_t M, int32_t K, uint32_t flags)
         L.counts_off = align_up(L.sums_off + (size_t)plan.groups * km * sizeof(double), 256);
         return align_up(L.counts_off + (size_t)plan.groups * K * sizeof(int32_t), 256);
     };
-    if (!L.l1_fused) L.plan = plan_for(select_path(M, K, flags), n, M, K, kAssignAccum);
+    // (an L1 run that is not fused sums from its labels)
+    const Mode mode = (flags & KMEANS_METRIC_L1) ? kAccumLabels : kAssignAccum;
+    if (!L.l1_fused) L.plan = plan_for(select_path(M, K, flags), n, M, K, mode);
     L.total = sized(L.plan);
     if (!L.l1_fused && use_split(M, K, flags)) {
         // two launches per iteration need fewer partial rows; the size that
@@ -565,6 +584,14 @@ int kmeans_update(const float *X, int64_t n, int32_t M, const int32_t *labels, i
     if (!aligned16(X)) return KMEANS_EINVAL;
     const Layout L = layout(n, M, K, 0);
     if (!workspace || workspace_bytes < L.total) return KMEANS_EWORKSPACE;
+    // the workspace is sized for the fused launch of a run; sums from labels
+    // alone need less LDS and may have more waves, or other workgroups (which
+    // walk the tiles with any number of them)
+    AccumPlan plan = L.plan;
+    if (plan.path == kPathTile) {
+        plan = plan_for(kPathTile, n, M, K, kAccumLabels);
+        if (plan.groups > L.plan.groups) plan.groups = L.plan.groups;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     StepArgs a{};
     a.X = X; a.n = n; a.M = M; a.C = prev_centers; a.K = K;
@@ -575,8 +602,8 @@ int kmeans_update(const float *X, int64_t n, int32_t M, const int32_t *labels, i
     a.fixed = 1;
     a.compare = 0;
     if ((rc = hip_status(launch_ctl_reset(a.ctl, s)))) return rc;
-    if ((rc = hip_status(launch_step(a, kAccumLabels, L.plan, s)))) return rc;
-    return hip_status(launch_centres(a, L.plan.groups, s));
+    if ((rc = hip_status(launch_step(a, kAccumLabels, plan, s)))) return rc;
+    return hip_status(launch_centres(a, plan.groups, s));
 }
 
 int kmeans_run(const float *X, int64_t n, int32_t M, int32_t K, const float *init_centers,

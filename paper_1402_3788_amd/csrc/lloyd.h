@@ -116,6 +116,8 @@ AccumPlan plan_tile(int64_t n, int M, int K, Mode mode);
 AccumPlan plan_accum(int64_t n, int M, int K);
 // Waves per workgroup of the tile kernel (0: its state does not fit in LDS).
 int tile_waves(int M, int K, Mode mode);
+// Whether its waves take turns at one slab when they sum from labels.
+bool tile_sums_in_turn(int M, int K);
 // Whether the tile kernel's per-workgroup state (centre operands and fp64
 // slab) fits in one workgroup's LDS for this shape.
 bool tile_fits(int M, int K);

@@ -56,7 +56,7 @@
 //              one slab per object of a step, or (when that leaves fewer
 //              waves) one slab that the objects of a step share, the LDS
 //              applying the lanes of one add in a fixed order; at the end the
-//              workgroup adds the slabs in a fixed order. Used while W >= 6
+//              workgroup adds the slabs in a fixed order. Used while W >= 6 (5)
 //              waves' private slabs fit in LDS (small K*M).
 //   ring    -- one fp64 slab per workgroup that the waves take turns to add
 //              their tiles into, in the fixed cyclic order wave 0, 1, ..., W-1
@@ -95,7 +95,11 @@ constexpr int kAccWave = 1;    // per-wave slabs, WaveAcc<M>::Pmax objects per s
 constexpr int kAccRing = 2;    // one slab per workgroup, waves add in turn
 constexpr int kAccWave1 = 3;   // one slab per wave, WaveAcc<M>::Pmax objects per step (less LDS)
 constexpr int kMaxWaves = 8;
-[[maybe_unused]] constexpr int kMinWaveForm = 6;   // fewest waves the wave form is used with
+// Fewest waves the wave form is used with: with distances six; without, a wave
+// spends its time on the sums and five with slabs of their own are the shorter
+// way (a kmeans_update of n = 400,000, M = 57, K = 32: 44.0 us with eight waves
+// in turn, 36.9 with five).
+[[maybe_unused]] constexpr int min_wave_form(int mode) { return mode == kAccumLabels ? 5 : 6; }
 
 // Candidates of an object in one lane (a quarter of the centres) up to which
 // fp64 distances to them decide; more are mostly resolved by the direct form.
@@ -158,9 +162,14 @@ __host__ __device__ constexpr int tile_slot(int M)
     return s > 2 * kWave ? s : 2 * kWave;
 }
 
-__host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc)
+// Rows of a wave form's slab: one more than there are clusters takes the adds
+// of close calls, which sums from labels do not have.
+__host__ __device__ inline int slab_rows(int K, int mode) { return mode == kAccumLabels ? K : K + 1; }
+
+// (sums from labels need no centre operands)
+__host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc, int mode)
 {
-    const int KT = centre_blocks(K);
+    const int KT = mode == kAccumLabels ? 0 : centre_blocks(K);
     MfmaLds L{};
     L.tile_floats = tile_slot(M);
     size_t o = 0;
@@ -169,9 +178,8 @@ __host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc)
     L.misc = o;    o = al16(o + 4 * (size_t)(2 * W + 1));  // the turn, the waves' counts and votes
     L.tiles = o;   o = al16(o + (size_t)W * L.tile_floats * 4);
     if (acc == kAccWave || acc == kAccWave1) {
-        // one row more than there are clusters takes the adds of close calls
         L.offs = o;    o = al16(o + (size_t)W * kWave * 4);
-        L.slab = o;    o = al16(o + (size_t)W * wave_acc_p(M, acc) * (K + 1) * (M + 1) * 8);
+        L.slab = o;    o = al16(o + (size_t)W * wave_acc_p(M, acc) * slab_rows(K, mode) * (M + 1) * 8);
     } else if (acc == kAccRing) {
         L.slab = o;    o = al16(o + (size_t)K * ring_row(M) * 8);
     }
@@ -181,17 +189,18 @@ __host__ __device__ inline MfmaLds mfma_lds(int M, int K, int W, int acc)
 
 // Close calls a wave can note: what the launch leaves of LDS. A launch argument,
 // so that the kernel makes no 64-bit division.
-[[maybe_unused]] inline int tile_list_cap(int M, int K, int W, int acc)
+[[maybe_unused]] inline int tile_list_cap(int M, int K, int W, int acc, int mode)
 {
-    const size_t o = mfma_lds(M, K, W, acc).list;
+    if (mode == kAccumLabels) return 0;
+    const size_t o = mfma_lds(M, K, W, acc, mode).list;
     const size_t left = o < (size_t)kMaxLds ? (size_t)kMaxLds - o : 0;
     const size_t cap = left / ((size_t)W * 8) / 2 * 2;
     return cap > (size_t)kMaxList ? kMaxList : (int)cap;
 }
 
-[[maybe_unused]] inline size_t tile_lds_bytes(int M, int K, int W, int acc)
+[[maybe_unused]] inline size_t tile_lds_bytes(int M, int K, int W, int acc, int mode)
 {
-    return mfma_lds(M, K, W, acc).list + (size_t)W * tile_list_cap(M, K, W, acc) * 8;
+    return mfma_lds(M, K, W, acc, mode).list + (size_t)W * tile_list_cap(M, K, W, acc, mode) * 8;
 }
 
 // Orders this wave's LDS accesses of different types (the hardware keeps a
@@ -259,7 +268,8 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     if (MODE != kAccumLabels && stop_before(ctl, t, fixed)) return;
     if (MODE == kAccumLabels && stop_after_assign(ctl, fixed)) return;
 
-    const MfmaLds L = mfma_lds(M, K, W, kAcc);
+    const MfmaLds L = mfma_lds(M, K, W, kAcc, MODE);
+    const int KR = slab_rows(K, MODE);
     float *tiles = reinterpret_cast<float *>(smem + L.tiles);
     float *tile = tiles + wave * kSlot;
     int32_t *offs = reinterpret_cast<int32_t *>(smem + L.offs) + wave * kWave;
@@ -268,7 +278,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     uint32_t *turn = reinterpret_cast<uint32_t *>(smem + L.misc);
     // (object, limit) of the close calls of this wave
     int2 *list = reinterpret_cast<int2 *>(smem + L.list) + (size_t)wave * lcap;
-    double *wslabs = reinterpret_cast<double *>(smem + L.slab) + (size_t)wave * kP * (K + 1) * (M + 1);
+    double *wslabs = reinterpret_cast<double *>(smem + L.slab) + (size_t)wave * kP * KR * (M + 1);
 
     // The grid works in rounds of G*W wave tiles; in round r, wave w of
     // workgroup b takes tile r*G*W + w*G + b. Rounds whose tiles are all full
@@ -296,7 +306,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
     // load the table of 1024 centres took 19 us, half of the launch.
     if (kWaveForm) {
         double *slabs = reinterpret_cast<double *>(smem + L.slab);
-        for (int i = tid; i < W * kP * (K + 1) * (M + 1); i += blockDim.x) slabs[i] = 0.0;
+        for (int i = tid; i < W * kP * KR * (M + 1); i += blockDim.x) slabs[i] = 0.0;
     } else if (kAcc == kAccRing) {
         double *slab = reinterpret_cast<double *>(smem + L.slab);
         for (int i = tid; i < K * ring_row(M); i += blockDim.x) slab[i] = 0.0;
@@ -627,7 +637,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
             // (labels read back may be out of range even in a full tile)
             if (have)
                 accumulate_tile<M, PA, kFullTile && MODE != kAccumLabels, kShared>(
-                    valid ? my_lab : -1, tile, offs, wslabs, K + 1, lane);
+                    valid ? my_lab : -1, tile, offs, wslabs, KR, lane);
         } else if (kAcc == kAccRing) {
             // This wave's turn of the step (every wave takes it, with or
             // without objects): lane l adds object l's features and count to
@@ -1084,7 +1094,7 @@ lloyd_tile_kernel(const float *__restrict__ X, int64_t n, const float *__restric
 
     if (kWaveForm) {
         __syncthreads();
-        write_wave_partials<M, PA, kShared>(reinterpret_cast<const double *>(smem + L.slab), W, K, K + 1,
+        write_wave_partials<M, PA, kShared>(reinterpret_cast<const double *>(smem + L.slab), W, K, KR,
                                part_sums + (int64_t)blockIdx.x * K * M,
                                part_counts + blockIdx.x, gridDim.x);
     } else if (kAcc == kAccRing) {
@@ -1160,12 +1170,13 @@ hipError_t LLOYD_PART_FN(launch_tile_part)(const StepArgs &a, Mode mode, const A
 namespace {
 
 // Most waves of a workgroup whose state fits in LDS with a list of kMinList
-// each, or one wave with what is left (0: not even one fits).
-int most_waves(int M, int K, int acc)
+// each (sums from labels note no close calls), or one wave with what is left
+// (0: not even one fits).
+int most_waves(int M, int K, int acc, Mode mode)
 {
     for (int w = kMaxWaves; w > 0; --w) {
-        if (tile_lds_bytes(M, K, w, acc) <= (size_t)kMaxLds &&
-            (w == 1 || tile_list_cap(M, K, w, acc) >= kMinList))
+        if (tile_lds_bytes(M, K, w, acc, mode) <= (size_t)kMaxLds &&
+            (w == 1 || mode == kAccumLabels || tile_list_cap(M, K, w, acc, mode) >= kMinList))
             return w;
     }
     return 0;
@@ -1173,19 +1184,19 @@ int most_waves(int M, int K, int acc)
 
 // Accumulation form and waves of an accumulating launch: private slabs (the
 // most objects per step that leaves the most waves) while at least
-// kMinWaveForm waves fit, else one shared slab, which leaves more waves.
-int accum_form(int M, int K, int &waves)
+// min_wave_form waves fit, else one shared slab, which leaves more waves.
+int accum_form(int M, int K, Mode mode, int &waves)
 {
-    const int w_p = most_waves(M, K, kAccWave), w_1 = most_waves(M, K, kAccWave1);
-    if (w_p >= kMinWaveForm && w_p >= w_1) {
+    const int w_p = most_waves(M, K, kAccWave, mode), w_1 = most_waves(M, K, kAccWave1, mode);
+    if (w_p >= min_wave_form(mode) && w_p >= w_1) {
         waves = w_p;
         return kAccWave;
     }
-    if (w_1 >= kMinWaveForm) {
+    if (w_1 >= min_wave_form(mode)) {
         waves = w_1;
         return kAccWave1;
     }
-    waves = most_waves(M, K, kAccRing);
+    waves = most_waves(M, K, kAccRing, mode);
     return kAccRing;
 }
 
@@ -1197,8 +1208,8 @@ AccumPlan plan_tile(int64_t n, int M, int K, Mode mode)
     p.path = kPathTile;
     const int64_t nq = (n + kWave - 1) / kWave;
     int W = kMaxWaves, acc = 0;
-    if (mode == kAssign) W = most_waves(M, K, 0);
-    else acc = accum_form(M, K, W);
+    if (mode == kAssign) W = most_waves(M, K, 0, mode);
+    else acc = accum_form(M, K, mode, W);
     // no more waves than there are 64-object tiles
     while (W > 1 && W / 2 >= nq) W /= 2;
     int64_t groups = (nq + W - 1) / W;
@@ -1206,8 +1217,8 @@ AccumPlan plan_tile(int64_t n, int M, int K, Mode mode)
     p.waves = W;
     p.groups = (int)groups;
     p.accum = acc;
-    p.list_cap = tile_list_cap(M, K, W, acc);
-    p.lds_bytes = tile_lds_bytes(M, K, W, acc);
+    p.list_cap = tile_list_cap(M, K, W, acc, mode);
+    p.lds_bytes = tile_lds_bytes(M, K, W, acc, mode);
     return p;
 }
 
@@ -1222,11 +1233,17 @@ bool tile_fits(int M, int K)
     return al16(table + norms + tile) + al16((size_t)K * ring_row(M) * 8) <= (size_t)kMaxLds;
 }
 
+bool tile_sums_in_turn(int M, int K)
+{
+    int W = 0;
+    return accum_form(M, K, kAccumLabels, W) == kAccRing;
+}
+
 int tile_waves(int M, int K, Mode mode)
 {
     int W = 0;
-    if (mode == kAssign) W = most_waves(M, K, 0);
-    else accum_form(M, K, W);
+    if (mode == kAssign) W = most_waves(M, K, 0, mode);
+    else accum_form(M, K, mode, W);
     return W;
 }
 
