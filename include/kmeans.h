@@ -167,10 +167,10 @@ int kmeans_centroid(const float *X, int64_t n, int32_t M, float *centroid, void 
                     size_t workspace_bytes, void *stream);
 
 /* Bytes of device workspace that kmeans_diameter needs: the centre of gravity
- * and its partials, four bf16 operand arrays of n * 32 ceil((M+2)/32) values
- * each (n rounded up to 16384), and 16 bytes per (512-object block, 16384-object
- * chunk) pair. 0 for refused shapes (also when n needs more than 65535 column
- * chunks). Pure host computation. */
+ * and its partials, four 16-bit arrays of n * 32 ceil((M+2)/32) values each (n
+ * rounded up to 16384: three of operands, one that holds the norms), and 16
+ * bytes per (512-object block, 16384-object chunk) pair. 0 for refused shapes
+ * (also when n needs more than 65535 column chunks). Pure host computation. */
 size_t kmeans_diameter_workspace_bytes(int64_t n, int32_t M);
 
 /*
@@ -188,7 +188,10 @@ size_t kmeans_diameter_workspace_bytes(int64_t n, int32_t M);
  * sqrt(*d2). The pairs are screened with fp16 matrix
  * products under a proven error bound and the close ones re-evaluated in
  * fp64, so the result is exact; the cost is two passes over all n(n-1)/2
- * pairs (O(n^2 M): about 0.1 s at n = 2*10^6, M = 25).
+ * pairs (O(n^2 M): about 0.1 s at n = 2*10^6, M = 25). Where very many pairs
+ * are within some 10^-5 of the longest distance (exact ties in numbers, points
+ * on a circle) the fp64 decisions take longer than the passes, up to about ten
+ * times in such sets.
  * Asynchronous on `stream`.
  */
 int kmeans_diameter(const float *X, int64_t n, int32_t M, double *d2, int32_t *pair,

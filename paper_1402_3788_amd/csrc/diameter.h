@@ -29,9 +29,10 @@ struct DiameterArgs {
     int M;
     float *centroid_ws;       // [M] centre of gravity (written by launch_centroid)
     float *norms;             // [n] squared norms of the centred objects
-    uint4 *ah, *bh;           // [npad][4 ks] fp16 operands
+    uint4 *ah, *bh, *low;     // [npad][4 ks] fp16 operands and their low parts
     uint32_t *counters;       // [0] largest |y|^2 (fp32 bits), [1] key of the pass-1 maximum,
-                              // [2] nonzero if X holds a NaN or an infinity
+                              // [2] nonzero if X holds a NaN or an infinity, [3] key of the
+                              // largest d~2 found, [4] pairs taken in fp64 (mod 2^32)
     DiamBest *slots;          // [row_blocks * chunks]
     double *d2;               // out: squared diameter
     int32_t *pair;            // out: [2] the pair

@@ -29,9 +29,12 @@
 //           key: order-free), and each work item's own maximum goes to its
 //           result slot;
 //   pass 2  items whose maximum is below the threshold d~* - 2B write an
-//           empty result at once; the others form the same products again,
-//           and every pair k < l with d~ >= d~* - 2B is re-evaluated in fp64
-//           in the fixed operation order
+//           empty result at once; the others form the same products again, and
+//           where a wave's 64 x 32 pairs hold one with d~ >= d~* - 2B, it adds
+//           the products with the operands' low parts, which gives values
+//           d~2 with a bound B2 some 300 times smaller. Of those the pairs
+//           k < l with d~2 >= (the largest d~2 found so far, by any wave) - 2
+//           B2 are re-evaluated in fp64 in the fixed operation order
 //           e = x_j - c_j, d = d + e*e (features ascending, each operation
 //           rounded) and the lexicographic best (largest d, then lowest k,
 //           then lowest l) is kept.
@@ -54,6 +57,25 @@
 // bf16 split products that this screening took before had a band of 0.06 % and
 // three times the matrix work: pass 1 at n = 500,003, M = 25 took 15.5 ms,
 // now 5.7.)
+//
+// The second screening. With v = s y, hi = fp16(v) (0 below 2^-14) and lo =
+// fp16(2^11 (v - hi)), written by the prep launch, the wave adds
+//   d~2 = d~ + 2^-11 sum(a_lo b_hi + a_hi b_lo),
+// the norms' remainders 2^11 (s^2 n - h - l) standing at feature M of a_lo and M
+// + 1 of b_lo against the ones of b_hi and a_hi. The true maximum is at least
+// any d~2 - B2 and a pair's d at most its d~2 + B2, so a pair left out is
+// strictly smaller than the maximum. B2 = 1.25 (2.02 E2 s^2 max_i n_i + A2),
+//   E2 = 4.01 u (centring) + 3.01 * 2^-22 (the dropped v_lo w_lo and lo's own
+//       rounding) + 1.01 * 2^-22 (the norms' remainders) + 1.01 gamma_M + 2.02
+//       phi_{P+2} + 2.02 u (the last addition) + 3.1 * 2^-11 phi_{2P+2} (the
+//       low sums, whose terms add up to at most 3.1 * 2^11 * 2^-11 (n_k + n_l)),
+//   A2 = 2^-10: lo below the normal range (2^-13), low times low where hi is 0
+//       (2^-13), h and l below it (2^-12), with 2^-11 more for the rest.
+// The pairs that remain wait in LDS until 64 of them are taken together, one per
+// lane. Without either, points on a circle (n = 20,000, M = 2) took 5,618 us and
+// two tight groups (M = 25) 1,069, and 3,305 and 685 with the bf16 products; now
+// 1,156 and 453 (n = 100,003: 9,425 and 1,290 with the bf16 products, now 3,525
+// and 642).
 //
 // Work: pass items are (row block of 512 objects, column chunk of 16384);
 // items wholly below the diagonal return at once, and within the diagonal
@@ -164,8 +186,9 @@ centroid_final_kernel(const double *__restrict__ part, int G, int M, int64_t n,
         if (centroid_ws) centroid_ws[j] = c;
         if (centroid_out) centroid_out[j] = c;
     }
-    // max norm, key of d~*, non-finite coordinate seen
-    if (counters && threadIdx.x < 3) counters[threadIdx.x] = 0;
+    // max norm, key of d~*, non-finite coordinate seen, key of the largest d~2,
+    // pairs taken in fp64
+    if (counters && threadIdx.x < 5) counters[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -220,12 +243,21 @@ __device__ inline int diam_scale_exp(const uint32_t *counters)
     return d >= 0 ? d / 2 : -((1 - d) / 2);       // floor(d / 2)
 }
 
+// High part of a scaled coordinate: its fp16 value, 0 below the normal range.
+__device__ inline float diam_high(float v)
+{
+    return fabsf(v) < 6.103515625e-5f ? 0.f : (float)(_Float16)v;
+}
+
+// Low parts are kept times 2^11, in the range of their high parts.
+constexpr int kLowExp = 11;
+
 // One thread per 16-byte group (8 features) of an operand row.
 __global__ void __launch_bounds__(256)
 diam_prep_kernel(const float *__restrict__ X, int64_t n, int64_t groups, int G4, int M,
                  const float *__restrict__ C, const float *__restrict__ norms,
                  const uint32_t *__restrict__ counters, uint4 *__restrict__ ah,
-                 uint4 *__restrict__ bh)
+                 uint4 *__restrict__ bh, uint4 *__restrict__ low_ops)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= groups) return;
@@ -234,32 +266,36 @@ diam_prep_kernel(const float *__restrict__ X, int64_t n, int64_t groups, int G4,
     const bool real = i < n;
     const bool low = M + 4 <= 8 * G4;             // room for the norms' low parts
     const int e = diam_scale_exp(counters);
-    h8v a, b;
-    float nh = 0.f, nl = 0.f;
+    h8v a, b, lo;
+    float nh = 0.f, nl = 0.f, rest = 0.f;
     if (real) {
         const float ns = ldexpf(norms[i], 2 * e);
         nh = (float)(_Float16)ns;
-        nl = ns - nh;
+        nl = (float)(_Float16)(ns - nh);
+        rest = ldexpf((ns - nh) - (low ? nl : 0.f), kLowExp);
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
         const int f = 8 * g + u;
-        float av = 0.f, bv = 0.f;
+        float av = 0.f, bv = 0.f, lv = 0.f;
         if (real && f < M) {
-            const float y = ldexpf(X[i * M + f] - C[f], e);
+            const float v = ldexpf(X[i * M + f] - C[f], e), y = diam_high(v);
             av = -2.0f * y;
             bv = y;
+            lv = ldexpf(v - y, kLowExp);
         } else if (real) {
-            if (f == M) { av = nh; bv = 1.0f; }
-            if (f == M + 1) { av = 1.0f; bv = nh; }
+            if (f == M) { av = nh; bv = 1.0f; lv = rest; }
+            if (f == M + 1) { av = 1.0f; bv = nh; lv = rest; }
             if (low && f == M + 2) { av = nl; bv = 1.0f; }
             if (low && f == M + 3) { av = 1.0f; bv = nl; }
         }
         a[u] = (_Float16)av;
         b[u] = (_Float16)bv;
+        lo[u] = (_Float16)lv;
     }
     ah[t] = __builtin_bit_cast(uint4, a);
     bh[t] = __builtin_bit_cast(uint4, b);
+    low_ops[t] = __builtin_bit_cast(uint4, lo);
 }
 
 // ---------------------------------------------------------------------------
@@ -270,26 +306,34 @@ __device__ inline bool diam_better(double d, int k, int l, double bd, int bk, in
     return d > bd || (d == bd && (k < bk || (k == bk && l < bl_)));
 }
 
+__device__ inline float round_down(double v)
+{
+    float t = (float)v;
+    if ((double)t > v) t = nextafterf(t, -INFINITY);
+    return t;
+}
+
 // Threshold of pass 2: d~* - 2B, rounded down to fp32; minus infinity (every
 // pair re-evaluated in fp64) when the largest norm is so large that an fp32
 // norm may overflow (a pair value is at most 4 max n_i), or so small that the
-// squares in it underflow, where the bound no longer holds.
+// squares in it underflow, where the bound no longer holds. band2: 2 B2.
 template <int KS>
-__device__ inline float diam_threshold(const uint32_t *counters, int M)
+__device__ inline float diam_threshold(const uint32_t *counters, int M, double &band2)
 {
     constexpr int P = 32 * KS;
     const double u = 5.9604644775390625e-8;           // 2^-24
     auto gamma = [&](int m) { return m * u / (1.0 - m * u); };
     auto phi = [&](int m) { return 2.0 * m * u / (1.0 - 2.0 * m * u); };
     const double norm_err = M + 4 <= P ? 1.01 / 4194304.0 : 1.01 / 2048.0;
-    const double E = 4.01 * u + 2.01 / 2048.0 + norm_err + 1.01 * gamma(M) + 2.02 * phi(P + 2);
+    const double sums = 4.01 * u + 1.01 * gamma(M) + 2.02 * phi(P + 2);
+    const double E = sums + 2.01 / 2048.0 + norm_err;
+    const double E2 = sums + 4.02 / 4194304.0 + 2.02 * u + 3.1 / 2048.0 * phi(2 * P + 2);
     const double maxn = (double)__uint_as_float(counters[0]);
     if (!(4.0 * maxn < (double)FLT_MAX) || maxn < 1e-30) return -INFINITY;
-    const double B = 1.25 * (2.02 * E * ldexp(maxn, 2 * diam_scale_exp(counters)) + 0.27);
-    const double thr = (double)key_float(counters[1]) - 2.0 * B;
-    float t = (float)thr;
-    if ((double)t > thr) t = nextafterf(t, -INFINITY);
-    return t;
+    const double scaled = 2.02 * ldexp(maxn, 2 * diam_scale_exp(counters));
+    const double B = 1.25 * (E * scaled + 0.27);
+    band2 = 2.0 * 1.25 * (E2 * scaled + 1.0 / 1024.0);
+    return round_down((double)key_float(counters[1]) - 2.0 * B);
 }
 
 // fp64 squared distance of objects i and j in the fixed operation order (the
@@ -308,11 +352,18 @@ __device__ __attribute__((noinline)) double diam_exact_d2(const float *__restric
     return d;
 }
 
+// Orders this wave's own LDS accesses (what its lanes wrote, its lanes read).
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <int KS, bool kExact>
 __device__ __forceinline__ void
 diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64_t n,
                int64_t nsteps_total, const float *__restrict__ X, int M,
-               uint32_t *__restrict__ counters, DiamBest *__restrict__ slots)
+               const uint4 *__restrict__ low_ops, uint32_t *__restrict__ counters, DiamBest *__restrict__ slots)
 {
     constexpr int G4 = 4 * KS;                        // 16-byte groups per operand row
     constexpr int kLdsRow = G4 + 1;                   // uint4 per LDS row (16 bytes padding)
@@ -337,11 +388,12 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64
     }
 
     float thr = 0.f;
+    double band2 = 0.0;
     if constexpr (kExact) {
         // pass 1 left this item's largest value in its slot: an item with no
         // value at the threshold has no candidate pair (a NaN, possible only
         // when thr is minus infinity, is kept)
-        thr = diam_threshold<KS>(counters, M);
+        thr = diam_threshold<KS>(counters, M, band2);
         if (slots[slot].d < (double)thr) {
             __syncthreads();                          // every thread has read the slot
             if (threadIdx.x == 0) slots[slot] = DiamBest{-1.0, INT_MAX, INT_MAX};
@@ -379,6 +431,23 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64
     int vmax = 0;
     double bd = -1.0;
     int bk = INT_MAX, bl_ = INT_MAX;
+    uint32_t taken = 0;                               // pairs in fp64 (whole wave)
+    // pairs that wait for fp64, 64 at a time: row - r0 and column - J0 of each
+    __shared__ uint32_t waiting[kExact ? kDiamWaves : 1][kExact ? 2 * kWave : 1];
+    int nwait = 0;
+    auto take = [&](int count) {
+        if (lane < count) {
+            const uint32_t q = waiting[w][lane];
+            const int64_t i = r0 + (q & 63u), j = J0 + (q >> 6);
+            const double d = diam_exact_d2(X, M, i, j);
+            if (diam_better(d, (int)i, (int)j, bd, bk, bl_)) {
+                bd = d;
+                bk = (int)i;
+                bl_ = (int)j;
+            }
+        }
+        taken += count;
+    };
 
     fetch(s_lo);
     stage(0);
@@ -432,25 +501,104 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64
             } else if (__builtin_amdgcn_ballot_w64(!(__int_as_float(smax) < thr)) != 0) {
                 // rare: some pair of this wave's half step reaches the threshold
                 const int64_t c0 = s * 64 + 32 * half;
+                float thr2 = thr;
+                if (thr > -INFINITY) {
+                    // rows of the low operands: object by object, the norm's
+                    // rest at both M and M + 1; as a's row times -2, 1 and 0,
+                    // as b's times 1, 0 and 1
+                    f4v lo[4][2];
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+                        for (int cc = 0; cc < 2; ++cc) lo[rb][cc] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const int g = ks * 4 + lane / 16;
+                        uint4 ra[4], rc[2];
+#pragma unroll
+                        for (int rb = 0; rb < 4; ++rb)
+                            ra[rb] = low_ops[(r0 + 16 * rb + lane % 16) * G4 + g];
+#pragma unroll
+                        for (int cc = 0; cc < 2; ++cc)
+                            rc[cc] = low_ops[(c0 + 16 * cc + lane % 16) * G4 + g];
+                        h8v ma, mb;
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const int f = 8 * g + u;
+                            ma[u] = (_Float16)(f < M ? -2.f : f == M ? 1.f : 0.f);
+                            mb[u] = (_Float16)(f == M ? 0.f : 1.f);
+                        }
+                        h8v bhi[2], blo[2];
+#pragma unroll
+                        for (int cc = 0; cc < 2; ++cc) {
+                            bhi[cc] = as_h8(lh[(32 * half + 16 * cc + lane % 16) * kLdsRow + g]);
+                            blo[cc] = as_h8(rc[cc]) * mb;
+                        }
+#pragma unroll
+                        for (int rb = 0; rb < 4; ++rb) {
+                            const h8v alo = as_h8(ra[rb]) * ma;
+#pragma unroll
+                            for (int cc = 0; cc < 2; ++cc) {
+                                lo[rb][cc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                    alo, bhi[cc], lo[rb][cc], 0, 0, 0);
+                                lo[rb][cc] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                    as_h8(a_op[rb][ks]), blo[cc], lo[rb][cc], 0, 0, 0);
+                            }
+                        }
+                    }
+                    // d~2 in place of d~, and its largest value (padding gives 0)
+                    float m = 0.f;
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+                        for (int cc = 0; cc < 2; ++cc)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                acc[rb][cc][r] = acc[rb][cc][r] + lo[rb][cc][r] * (1.0f / 2048.0f);
+                                m = fmaxf(m, acc[rb][cc][r]);
+                            }
+#pragma unroll
+                    for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+                    const uint32_t key = float_key(m);
+                    uint32_t best = __hip_atomic_load(&counters[3], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+                    if (key > best) {
+                        if (lane == 0) atomicMax(&counters[3], key);
+                        best = key;
+                    }
+                    thr2 = round_down((double)key_float(best) - band2);
+                }
+                // this lane's values at the threshold, one bit each (a NaN,
+                // possible only when thr is minus infinity, is taken too)
+                uint32_t mask = 0;
 #pragma unroll
                 for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
                     for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int64_t i = r0 + 16 * rb + 4 * (lane / 16) + r;
-                            const int64_t j = c0 + 16 * cc + lane % 16;
-                            // (a NaN value, possible only when thr is minus
-                            // infinity, is re-evaluated too)
-                            if (!(acc[rb][cc][r] < thr) && i < j && j < n) {
-                                const double d = diam_exact_d2(X, M, i, j);
-                                if (diam_better(d, (int)i, (int)j, bd, bk, bl_)) {
-                                    bd = d;
-                                    bk = (int)i;
-                                    bl_ = (int)j;
-                                }
-                            }
-                        }
+                        for (int r = 0; r < 4; ++r)
+                            if (!(acc[rb][cc][r] < thr2)) mask |= 1u << (8 * rb + 4 * cc + r);
+                while (__builtin_amdgcn_ballot_w64(mask != 0u) != 0) {
+                    const int b = mask != 0u ? __ffs(mask) - 1 : 0;
+                    const int row = 16 * (b >> 3) + 4 * (lane / 16) + (b & 3);
+                    const int64_t j = c0 + 16 * ((b >> 2) & 1) + lane % 16;
+                    const bool close = mask != 0u && r0 + row < j && j < n;
+                    mask &= mask - 1u;
+                    const uint64_t vote = __builtin_amdgcn_ballot_w64(close);
+                    if (close)
+                        waiting[w][nwait + __popcll(vote & ((1ull << lane) - 1ull))] =
+                            (uint32_t)row | (uint32_t)(j - J0) << 6;
+                    nwait += __popcll(vote);
+                    wave_lds_fence();
+                    if (nwait >= kWave) {
+                        take(kWave);
+                        nwait -= kWave;
+                        const uint32_t left = waiting[w][kWave + lane];
+                        wave_lds_fence();
+                        if (lane < nwait) waiting[w][lane] = left;
+                        wave_lds_fence();
+                    }
+                }
             }
         }
 
@@ -471,6 +619,7 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64
             slots[slot] = DiamBest{(double)v, INT_MAX, INT_MAX};   // read by pass 2
         }
     } else {
+        take(nwait);
 #pragma unroll
         for (int off = kWave / 2; off > 0; off >>= 1) {
             const double d2 = __shfl_xor(bd, off);
@@ -481,7 +630,10 @@ diam_pass_body(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64
                 bl_ = l2;
             }
         }
-        if (lane == 0) wbest[w] = DiamBest{bd, bk, bl_};
+        if (lane == 0) {
+            wbest[w] = DiamBest{bd, bk, bl_};
+            if (taken != 0) atomicAdd(&counters[4], taken);
+        }
         __syncthreads();
         if (threadIdx.x == 0) {
             DiamBest b = wbest[0];
@@ -496,9 +648,10 @@ template <int KS, bool kExact>
 __global__ void __launch_bounds__(kDiamThreads)
 diam_pass_kernel(const uint4 *__restrict__ ah, const uint4 *__restrict__ bh, int64_t n,
                  int64_t nsteps_total, const float *__restrict__ X, int M,
-                 uint32_t *__restrict__ counters, DiamBest *__restrict__ slots)
+                 const uint4 *__restrict__ low_ops, uint32_t *__restrict__ counters,
+                 DiamBest *__restrict__ slots)
 {
-    diam_pass_body<KS, kExact>(ah, bh, n, nsteps_total, X, M, counters, slots);
+    diam_pass_body<KS, kExact>(ah, bh, n, nsteps_total, X, M, low_ops, counters, slots);
 }
 
 // The lexicographic best of all item slots. With n = 1 there is no pair:
@@ -563,17 +716,17 @@ hipError_t diam_launch_ks(const DiameterArgs &a, const DiameterPlan &pl, hipStre
     const int64_t groups = pl.npad * 4 * KS;
     hipLaunchKernelGGL(diam_prep_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s,
                        a.X, a.n, groups, 4 * KS, a.M, a.centroid_ws, a.norms, a.counters, a.ah,
-                       a.bh);
+                       a.bh, a.low);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 grid((unsigned)pl.row_blocks, (unsigned)pl.chunks);
     const int64_t nsteps = pl.npad / 64;
     auto pass1 = diam_pass_kernel<KS, false>;
     auto pass2 = diam_pass_kernel<KS, true>;
     hipLaunchKernelGGL(pass1, grid, dim3(kDiamThreads), 0, s, a.ah, a.bh, a.n,
-                       nsteps, a.X, a.M, a.counters, a.slots);
+                       nsteps, a.X, a.M, a.low, a.counters, a.slots);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(pass2, grid, dim3(kDiamThreads), 0, s, a.ah, a.bh, a.n,
-                       nsteps, a.X, a.M, a.counters, a.slots);
+                       nsteps, a.X, a.M, a.low, a.counters, a.slots);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(diam_final_kernel, dim3(1), dim3(1024), 0, s, a.slots,
                        (int64_t)pl.row_blocks * pl.chunks, a.n, a.counters, a.d2, a.pair);

@@ -195,9 +195,9 @@ InitLayout init_layout(int64_t n, int32_t M)
 }
 
 // Workspace of the centroid and diameter launches: [counters 256 B]
-// [fp32 centroid, M] [fp64 partials G*M] then, for the diameter, two operand
-// arrays [npad][4 ks] x 16 B, the norms [n] (in room for two more such arrays:
-// the size that callers see has not changed) and the item slots.
+// [fp32 centroid, M] [fp64 partials G*M] then, for the diameter, three operand
+// arrays [npad][4 ks] x 16 B, the norms [n] (in the room of one more) and the
+// item slots.
 struct DiamLayout {
     CentroidPlan cplan;
     DiameterPlan dplan;
@@ -540,7 +540,8 @@ int kmeans_diameter(const float *X, int64_t n, int32_t M, double *d2, int32_t *p
     a.centroid_ws = reinterpret_cast<float *>(ws + L.centroid_off);
     a.ah = reinterpret_cast<uint4 *>(ws + L.ops_off);
     a.bh = reinterpret_cast<uint4 *>(ws + L.ops_off + L.ops_bytes);
-    a.norms = reinterpret_cast<float *>(ws + L.ops_off + 2 * L.ops_bytes);
+    a.low = reinterpret_cast<uint4 *>(ws + L.ops_off + 2 * L.ops_bytes);
+    a.norms = reinterpret_cast<float *>(ws + L.ops_off + 3 * L.ops_bytes);
     a.slots = reinterpret_cast<DiamBest *>(ws + L.slots_off);
     a.d2 = d2;
     a.pair = pair;

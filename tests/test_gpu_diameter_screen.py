@@ -42,3 +42,41 @@ def test_screening_keeps_the_farthest_pair(M, scale, kind):
     want = oracle.diameter(X)
     assert float(d2.item()) == float(want[0])
     assert tuple(pair.cpu().tolist()) == want[1:]
+
+
+def _band_pairs(X):
+    """Pairs within 0.4 % of the largest centred norm of the longest: in the
+    band of the first screening whatever its products round to."""
+    x = X.astype(np.float64) - X.astype(np.float64).mean(axis=0)
+    nrm = (x * x).sum(axis=1)
+    d = nrm[:, None] + nrm[None, :] - 2.0 * (x @ x.T)
+    return int((d >= d.max() - 0.004 * nrm.max()).sum()) // 2
+
+
+def _counted(X):
+    """Diameter of X, and the pairs that were taken in fp64: the fifth counter
+    at the workspace's start."""
+    n, M = X.shape
+    ws = torch.empty(km.kmeans_diameter_workspace_bytes(n, M), dtype=torch.uint8, device=DEV)
+    d2, pair, _ = km.kmeans_diameter(torch.from_numpy(X).to(DEV), ws=ws)
+    return float(d2.item()), tuple(pair.cpu().tolist()), int(ws[16:20].cpu().view(torch.int32).item())
+
+
+@pytest.mark.parametrize("M,kind", [(2, "sphere"), (3, "sphere")] +
+                         [(M, "groups") for M in (2, 3, 25, 29, 32, 62, 64)])
+def test_few_of_many_pairs_near_the_longest_are_taken_in_fp64(M, kind):
+    """Points on a sphere, and two groups of sigma 3e-5 at distance 1."""
+    print(f"[screen] M={M} {kind}", flush=True)
+    rng = np.random.default_rng(M)
+    X = rng.standard_normal((3_001, M))
+    if kind == "sphere":
+        X /= np.linalg.norm(X, axis=1, keepdims=True)
+    else:
+        X *= 3e-5
+        X[1_500:, 0] += 1.0
+    X = np.ascontiguousarray(X.astype(np.float32))
+    d2, pair, taken = _counted(X)
+    want = oracle.diameter(X)
+    assert (d2, pair) == (float(want[0]), want[1:])
+    print(f"[screen] {taken} pairs", flush=True)
+    assert 1 <= taken < _band_pairs(X) // 4
