@@ -316,7 +316,8 @@ __device__ inline float round_down(double v)
 // Threshold of pass 2: d~* - 2B, rounded down to fp32; minus infinity (every
 // pair re-evaluated in fp64) when the largest norm is so large that an fp32
 // norm may overflow (a pair value is at most 4 max n_i), or so small that the
-// squares in it underflow, where the bound no longer holds. band2: 2 B2.
+// squares in it underflow by more than the margin covers: M of them lose at
+// most M 2^-150 = 4.5e-44 together, 0.08 u of 1e-35. band2: 2 B2.
 template <int KS>
 __device__ inline float diam_threshold(const uint32_t *counters, int M, double &band2)
 {
@@ -329,7 +330,7 @@ __device__ inline float diam_threshold(const uint32_t *counters, int M, double &
     const double E = sums + 2.01 / 2048.0 + norm_err;
     const double E2 = sums + 4.02 / 4194304.0 + 2.02 * u + 3.1 / 2048.0 * phi(2 * P + 2);
     const double maxn = (double)__uint_as_float(counters[0]);
-    if (!(4.0 * maxn < (double)FLT_MAX) || maxn < 1e-30) return -INFINITY;
+    if (!(4.0 * maxn < (double)FLT_MAX) || maxn < 1e-35) return -INFINITY;
     const double scaled = 2.02 * ldexp(maxn, 2 * diam_scale_exp(counters));
     const double B = 1.25 * (E * scaled + 0.27);
     band2 = 2.0 * 1.25 * (E2 * scaled + 1.0 / 1024.0);

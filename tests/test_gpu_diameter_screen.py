@@ -80,3 +80,16 @@ def test_few_of_many_pairs_near_the_longest_are_taken_in_fp64(M, kind):
     assert (d2, pair) == (float(want[0]), want[1:])
     print(f"[screen] {taken} pairs", flush=True)
     assert 1 <= taken < _band_pairs(X) // 4
+
+
+@pytest.mark.parametrize("scale", [1e-15, 1e-16, 1e-17, 2e-18])
+@pytest.mark.parametrize("M", [5, 25, 64])
+def test_small_spreads_are_screened(M, scale):
+    """Squared norms down to 1e-35 are screened like any others."""
+    print(f"[screen] M={M} scale={scale}", flush=True)
+    X = np.ascontiguousarray((_data(3_001, M, "normal", M) * scale).astype(np.float32))
+    d2, pair, taken = _counted(X)
+    want = oracle.diameter(X)
+    assert (d2, pair) == (float(want[0]), want[1:])
+    print(f"[screen] {taken} pairs", flush=True)
+    assert 1 <= taken < 1_000
