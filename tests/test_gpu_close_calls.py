@@ -16,6 +16,7 @@ import torch
 
 import oracle
 import paper_1402_3788_amd as km
+import test_plans
 
 pytestmark = pytest.mark.gpu
 
@@ -85,9 +86,11 @@ def test_overflowing_lists_follow_the_oracle(n, M, K, path):
 
 @pytest.mark.parametrize("with_d2", [False, True])
 def test_overflowing_lists_of_the_lane_kernel(with_d2):
-    """More close calls per wave than the list holds (470 beside the slabs of
+    """More close calls per wave than the list holds (444 beside the slabs of
     K = 64, M = 32): the labels equal those of the direct form, whose calls do
-    not go through a list, and the centres to one unit in the last place."""
+    not go through a list, and the centres to one unit in the last place.
+    (Without distances to overflow, the assignment alone fits its longer lists
+    here; test_every_kind_of_list_overflows has the sizes for it.)"""
     n, M, K = 1_200_003, 32, 64
     print(f"[overflow lane] n={n} M={M} K={K}", flush=True)
     X, C = _case(n, M, K, 5, "offset")
@@ -105,11 +108,48 @@ def test_overflowing_lists_of_the_lane_kernel(with_d2):
     assert ((cen - wcen).abs() <= 2.0**-23 * scale).all()
 
 
+@pytest.mark.parametrize("n,M,K,kernel,mode", [
+    (4_300_003, 3, 64, "lane", "assign"), (920_009, 32, 64, "lane", "run"),
+    (460_003, 64, 186, "tile", "assign"), (550_003, 40, 20, "tile", "run"),
+    (1_010_009, 17, 100, "tile", "run"), (570_011, 25, 300, "tile", "run"),
+    (1_860_001, 33, 65, "tile", "run")])
+def test_every_kind_of_list_overflows(n, M, K, kernel, mode):
+    """Every centre is there twice, so every object is open, and there are more
+    objects than all lists hold together: the assignments with and without
+    distances, private slabs (two forms) and slabs that six or eight waves
+    share in turn."""
+    print(f"[overflow] n={n} M={M} K={K} {kernel} {mode}", flush=True)
+    plan = test_plans.plan_tile if kernel == "tile" else test_plans.plan_lane_mfma
+    p = plan(n, M, K, test_plans.ASSIGN if mode == "assign" else test_plans.ASSIGN_ACCUM)
+    assert p.waves >= 6 and n > p.waves * p.groups * p.list_cap
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    X = torch.randn(n, M, device=DEV, generator=g)
+    C = torch.randn(K, M, device=DEV, generator=g)
+    C[K // 2:K // 2 * 2] = C[:K // 2]
+    if K % 2:
+        C[K - 1] = 1e6                          # the nearest of no object
+    ws = km.workspace(n, M, K, DEV)
+    lab, cen, cnt, _ = km.kmeans_run(X, K, C, 1, fixed_iters=True, ws=ws)
+    want, wd2 = km.kmeans_assign(X, C, with_min_d2=True, path="direct")
+    assert km.ctl_fallbacks(ws) == n            # all open
+    assert torch.equal(lab, want)
+    wcen, wcnt = km.kmeans_update(X, want, K, C)
+    assert torch.equal(cnt, wcnt)
+    scale = wcen.abs().amax(1, keepdim=True)
+    assert ((cen - wcen).abs() <= 2.0**-23 * scale).all()
+    if mode == "assign":
+        assert torch.equal(km.kmeans_assign(X, C), want)
+        lab, d2 = km.kmeans_assign(X, C, with_min_d2=True)
+        assert torch.equal(lab, want)
+        torch.testing.assert_close(d2, wd2, rtol=(M + 2) * 2.0**-22, atol=1e-30)
+
+
 @pytest.mark.parametrize("n,M,K", [(1, 16, 1024), (64, 16, 1024), (65, 63, 260), (40_007, 15, 1000),
                                    (40_007, 64, 256), (9_999, 41, 399)])
 def test_sums_from_labels_follow_the_oracle(n, M, K):
-    """The sums' own launch, by slices of four features (M a multiple of four
-    or not, labels out of range ignored)."""
+    """The sums' own launch, by slices of features (M a multiple of four or
+    not, labels out of range ignored)."""
     print(f"[sums] n={n} M={M} K={K}", flush=True)
     rng = np.random.default_rng(n + M)
     X = rng.uniform(-60, 60, (n, M)).astype(np.float32)
