@@ -41,11 +41,11 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // Distance path. KMEANS_PATH_DIRECT: the vector ALU. KMEANS_PATH_TILES: the
 // 64-object tiles (-1 when their workgroup state does not fit in LDS).
 // KMEANS_PATH_MFMA: the
-// matrix cores, one object per lane when the centre operands fit in registers
-// (K <= 16, M <= 32), else 64-object tiles when their workgroup state fits in
-// LDS, else -1 (refused). No flag: tiles for K > 16, one object per lane on the
-// matrix cores for 5 <= K <= 16, the vector ALU otherwise (and wherever the
-// matrix-core forms do not fit).
+// matrix cores, one object per lane for K <= 64 and M <= 32, else 64-object
+// tiles when their workgroup state fits in LDS, else -1 (refused). No flag: one
+// object per lane on the matrix cores for 5 <= K <= 64 and M <= 32, tiles for
+// K > 16 otherwise, and the vector ALU for the rest (K <= 4, 5 <= K <= 16 with
+// M > 32, and wherever the matrix-core forms do not fit).
 int select_path(int32_t M, int32_t K, uint32_t flags)
 {
     if (flags & KMEANS_PATH_DIRECT) return kPathValu;

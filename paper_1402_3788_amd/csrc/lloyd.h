@@ -71,7 +71,7 @@ enum Mode : int {
 
 // Distance paths: one object per lane with the direct form on the vector ALU
 // (lloyd_lane.hip), one object per lane with the scores on the bf16 matrix
-// cores (lloyd_lane_mfma.hip, K <= 16), or 64-object tiles on the matrix cores
+// cores (lloyd_lane_mfma.hip, K <= 64 and M <= 32), or 64-object tiles on the matrix cores
 // with a cross-lane argmin (lloyd_tile.hip, any K). kPathSplit: the tile
 // kernel assigns only, and the sums come from its labels in a launch of their
 // own (lloyd_accum.hip).
@@ -122,7 +122,7 @@ bool tile_sums_in_turn(int M, int K);
 // slab) fits in one workgroup's LDS for this shape.
 bool tile_fits(int M, int K);
 // Whether the one-object-per-lane matrix-core form supports this shape (its
-// centre operands live in registers: K <= 16, M <= 32).
+// centre operands live in registers or LDS: K <= 64, M <= 32).
 bool lane_mfma_fits(int M, int K);
 // Where that form's table of slab offsets starts in LDS (bytes).
 size_t lane_mfma_offs_at(int M, int K, int W);

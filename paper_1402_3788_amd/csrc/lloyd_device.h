@@ -180,37 +180,6 @@ __device__ inline float second_of(float b1, float b2, float p1, float p2)
     return __builtin_amdgcn_fmed3f(b1, p1, fminf(b2, p2));
 }
 
-// Merge the (best, second, label) triples of lanes l and l ^ 16 (ROW = 16) or
-// l and l ^ 32 (ROW = 32): the row swap returns, in every lane, the triples of
-// both lanes of its pair; the merge keeps the lower label on equal scores.
-template <int ROW>
-__device__ inline void merge_rows(float &b1, float &b2, int &lb)
-{
-    auto swap = [](uint32_t v) {
-        if (ROW == 16) return __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        return __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    };
-    const auto s1 = swap(__float_as_uint(b1));
-    const auto s2 = swap(__float_as_uint(b2));
-    const auto sl = swap((uint32_t)lb);
-    const float f1 = __uint_as_float(s1[0]), g1 = __uint_as_float(s1[1]);
-    const float f2 = __uint_as_float(s2[0]), g2 = __uint_as_float(s2[1]);
-    const int fl = (int)sl[0], gl = (int)sl[1];
-    const bool take = (g1 < f1) | ((g1 == f1) & (gl < fl));
-    b2 = second_of(f1, f2, g1, g2);
-    b1 = take ? g1 : f1;
-    lb = take ? gl : fl;
-}
-
-template <int ROW>
-__device__ inline float sum_rows(float v)
-{
-    uint32_t u = __float_as_uint(v);
-    const auto s = (ROW == 16) ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
-                               : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-
 // Packed (best, second) keys of object `lane` (column lane / 16 of the tile's
 // 16-object columns) from the per-column keys (k1[c], k2[c]) of the four lanes
 // l16 + 16 g' that hold its centre rows. Two exchange stages: with lane l ^ 32
@@ -223,7 +192,8 @@ __device__ inline void own_column_keys(const float (&k1)[4], const float (&k2)[4
 {
     const bool up = lane >= 32;
     const bool odd = (lane >> 4) & 1;
-    // the partner's value out of a swap's pair (see merge_rows)
+    // the partner's value: the swap returns, in every lane, those of both
+    // lanes of its pair
     auto other32 = [up](uint32_t v) {
         const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
         return __uint_as_float(up ? r[0] : r[1]);
@@ -308,7 +278,9 @@ __device__ inline void accumulate_tile(int lab, const float *tile, int32_t *offs
     if constexpr (kFull && M + 1 <= kWave) {
         if (used) {
             double *col = slabs + j;
-            // 1.0f the optimiser cannot see through (see accumulate_commit)
+            // 1.0f the optimiser cannot see through, so the count lane's select
+            // stays one 32-bit select ahead of the conversion instead of two
+            // 32-bit selects on the converted double
             float one;
             asm("v_mov_b32 %0, 1.0" : "=v"(one));
 #pragma unroll
@@ -341,85 +313,6 @@ __device__ inline void accumulate_tile(int lab, const float *tile, int32_t *offs
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const double v = (double)(feat ? x[b] : 1.0f);
-                if (used && o[b] >= 0)
-                    __hip_atomic_fetch_add(slabs + o[b] + j, v, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WAVEFRONT);
-                if (M + 1 > kWave && lane == 0 && o[b] >= 0)   // M = 64: no lane left for the count
-                    __hip_atomic_fetch_add(slabs + o[b] + M, 1.0, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WAVEFRONT);
-            }
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-// The same accumulation in two parts, so the tile's feature reads (which do
-// not depend on the labels) can be issued before the assignment and wait in
-// registers: accumulate_fetch reads every step's value for this lane,
-// accumulate_commit adds them once the labels are known.
-template <int M, int P_>
-struct AccFetch {
-    float x[WaveAcc<M, P_>::kSteps];
-};
-
-template <int M, int P_>
-__device__ inline void accumulate_fetch(const float *tile, int lane, AccFetch<M, P_> &f)
-{
-    using A = WaveAcc<M, P_>;
-    constexpr int LW = A::LW, P = A::P;
-    const int h = lane / LW, j = lane % LW;
-    const float *xp = tile + h * M + (j < M ? j : M);
-#pragma unroll
-    for (int s = 0; s < A::kSteps; ++s) f.x[s] = xp[s * P * M];
-}
-
-// kFull: every object of the tile is present (lab >= 0 in every lane), so the
-// per-step validity test drops out and the lanes past the count column are
-// masked once for the whole tile.
-template <int M, int P_, bool kFull = false>
-__device__ inline void accumulate_commit(int lab, const AccFetch<M, P_> &f, int32_t *offs,
-                                         double *slabs, int K, int lane)
-{
-    using A = WaveAcc<M, P_>;
-    constexpr int MW = A::MW, LW = A::LW, P = A::P;
-    offs[lane] = (kFull || lab >= 0) ? ((lane % P) * K + lab) * MW : -1;
-    __builtin_amdgcn_wave_barrier();
-    const int h = lane / LW, j = lane % LW;
-    const int32_t *op = offs + h;
-    const bool feat = j < M;
-    const bool used = j <= M;
-    constexpr int B = A::kSteps < 16 ? A::kSteps : 16;
-    if constexpr (kFull && M + 1 <= kWave) {
-        if (used) {
-            double *col = slabs + j;
-            // 1.0f the optimiser cannot see through, so the count lane's select
-            // stays one 32-bit select ahead of the conversion instead of two
-            // 32-bit selects on the converted double
-            float one;
-            asm("v_mov_b32 %0, 1.0" : "=v"(one));
-#pragma unroll
-            for (int s0 = 0; s0 < A::kSteps; s0 += B) {
-                int o[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b) o[b] = op[(s0 + b) * P];
-#pragma unroll
-                for (int b = 0; b < B; ++b) {
-                    // the count column adds 1 (exact in fp64)
-                    const float x = feat ? f.x[s0 + b] : one;
-                    __hip_atomic_fetch_add(col + o[b], (double)x, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WAVEFRONT);
-                }
-            }
-        }
-    } else {
-#pragma unroll
-        for (int s0 = 0; s0 < A::kSteps; s0 += B) {
-            int o[B];
-#pragma unroll
-            for (int b = 0; b < B; ++b) o[b] = op[(s0 + b) * P];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const double v = feat ? (double)f.x[s0 + b] : 1.0;
                 if (used && o[b] >= 0)
                     __hip_atomic_fetch_add(slabs + o[b] + j, v, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WAVEFRONT);

@@ -66,7 +66,9 @@ constexpr int kL1 = 1;
 [[maybe_unused]] constexpr int kL1FewTilesK = 20;
 [[maybe_unused]] constexpr int kL1FewTilesM = 37;
 // Sums of a workgroup up to which few tiles are spread (256 rows of 2048
-// sums: 4 MB of partials).
+// sums: 4 MB of partials). Every shape that comes here unasked is below it (K <=
+// 4, K <= 16 with M > 32, fused L1 with K <= 32); it holds back the partials of
+// those that ask for the direct path with more centres.
 [[maybe_unused]] constexpr int kSpreadKM = 2048;
 
 // Per-wave tile slot: the 64 objects plus slack.

@@ -1011,7 +1011,7 @@ size_t lane_mfma_offs_at(int M, int K, int W) { return lane_offs_at(M, K, W); }
 
 bool lane_mfma_fits(int M, int K)
 {
-    return K <= kMaxKLane && M <= kMaxMLane;   // (the slabs of K = 64, M = 32 leave 470 list places)
+    return K <= kMaxKLane && M <= kMaxMLane;   // (the slabs of K = 64, M = 32 leave 444 list places)
 }
 
 AccumPlan plan_lane_mfma(int64_t n, int M, int K, Mode mode)
