@@ -139,6 +139,19 @@ struct Layout {
     size_t sums_off, counts_off, total;
 };
 
+// Waves of the tile kernel that LDS holds beside the centre operands and one
+// slab of sums, lists of close calls left out.
+int tile_waves_without_lists(int32_t M, int32_t K)
+{
+    const size_t fixed = align_up((size_t)((K + 15) / 16) * ((M + 31) / 32) * kWave * 32, 16) +
+                         align_up((size_t)((K + 15) / 16) * 64, 16) + 16 +
+                         align_up((size_t)K * ((M + 1) | 1) * 8, 16);
+    const size_t tile = align_up((size_t)((kWave * M + (M > 4 ? M : 4) + 3) / 4 * 4) * 4, 16);
+    int W = 8;
+    while (W > 1 && fixed + W * tile > (size_t)kMaxLds) --W;
+    return W;
+}
+
 Layout layout(int64_t n, int32_t M, int32_t K, uint32_t flags)
 {
     Layout L{};
@@ -157,6 +170,20 @@ Layout layout(int64_t n, int32_t M, int32_t K, uint32_t flags)
     const Mode mode = (flags & KMEANS_METRIC_L1) ? kAccumLabels : kAssignAccum;
     if (!L.l1_fused) L.plan = plan_for(select_path(M, K, flags), n, M, K, mode);
     L.total = sized(L.plan);
+    if (L.plan.path == kPathTile && L.total > KMEANS_NOALLOC_MAX_WORKSPACE) {
+        // the lists leave fewer waves per workgroup, so few objects make more
+        // workgroups and rows of partials; a call whose rows fit the static
+        // workspace without lists keeps to the rows that fit (n = 70,000, M = 17,
+        // K = 473: 12.1 MB, with the lists 17.0, refused by kmeans_run_noalloc)
+        const int64_t tiles = (n + kWave - 1) / kWave, W = tile_waves_without_lists(M, K);
+        AccumPlan few = L.plan;
+        few.groups = (int)((tiles + W - 1) / W < kCUs ? (tiles + W - 1) / W : kCUs);
+        if (sized(few) <= KMEANS_NOALLOC_MAX_WORKSPACE)
+            while (L.total > KMEANS_NOALLOC_MAX_WORKSPACE) {
+                --L.plan.groups;
+                L.total = sized(L.plan);
+            }
+    }
     if (!L.l1_fused && use_split(M, K, flags)) {
         // two launches per iteration need fewer partial rows; the size that
         // callers see (and that decides what fits the static workspace) stays

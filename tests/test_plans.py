@@ -101,3 +101,11 @@ def test_sums_in_slices_fill_the_chip_within_lds():
                 assert slices * -(-n // (64 * p.waves)) >= 256
     assert plan_accum(400_000, 57, 140).accum == 16
     assert plan_accum(16_384, 25, 400).accum == 4
+
+
+@pytest.mark.parametrize("n,M,K", [(70_000, 17, 473), (16_384, 17, 525), (100_000, 18, 447),
+                                   (100_000, 28, 295), (70_000, 22, 386), (20_011, 18, 525)])
+def test_lists_do_not_push_few_objects_out_of_the_static_workspace(n, M, K):
+    """Shapes whose partials fit it with the waves that LDS holds without lists."""
+    for flags in (0, 4, 8):
+        assert 0 < km.kmeans_workspace_bytes(n, M, K, flags) <= km.NOALLOC_MAX_WORKSPACE

@@ -57,3 +57,10 @@ def test_noalloc_refuses_oversized_workspace():
     # and a call that fits still works afterwards
     Xs, Cs = workloads.random_case(10_000, 25, 16, seed=3, kind="blobs")
     _both(Xs, Cs, 16, 20, False)
+
+
+@pytest.mark.parametrize("n,M,K,path", [(16_384, 17, 525, None), (70_000, 22, 386, "tiles")])
+def test_noalloc_keeps_to_the_rows_that_fit(n, M, K, path):
+    print(f"[noalloc] n={n} M={M} K={K} path={path}", flush=True)
+    X, C0 = workloads.random_case(n, M, K, seed=n, kind="blobs")
+    _both(X, C0, K, 4, True, path=path)
